@@ -17,8 +17,8 @@
 //
 // Decomposition and placement.  A workgroup owns one query block of one env
 // (64 rows on the fp32 path; up to 128 rows as eight 16-row waves, the env's
-// row waves spread evenly over its blocks, or 32 rows as one wave pair, on
-// the bf16 path) and a contiguous range of 64-key tiles (a key split); the
+// row waves spread evenly over its blocks, 128 rows as two wave teams, or 32
+// rows as one wave pair, on the bf16 path) and a contiguous range of 64-key tiles (a key split); the
 // dynamic tile comes last.  All query blocks of one (env,
 // split) group share the same K/V tiles, so the 1-D grid is laid out such
 // that a group's blocks are dispatched to the same XCD (workgroups go
@@ -624,6 +624,12 @@ RFX_DEV float xsum16_32(float v) {
 RFX_DEV void lds_dma16(const void* g, void* lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                :: "v"(g), "s"((unsigned)(size_t)lds) : "memory");
+}
+
+// The same from a wave-uniform base and a 32-bit byte offset per lane.
+RFX_DEV void lds_dma16(const void* base, uint32_t off, void* lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(off), "s"(base), "s"((unsigned)(size_t)lds) : "memory");
 }
 
 template <int DH>
@@ -1236,13 +1242,527 @@ __global__ __launch_bounds__(128) void attn_pair_kernel(AttnArgs p) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// bf16 variant with wave teams, for a few envs with more keys than one tile per
+// workgroup (heads of 128 or 256).
+//
+// A workgroup holds up to 128 query rows as two teams of four waves; a team
+// owns up to 64 rows (two 32-row blocks).  Each 64-key tile is staged once in
+// LDS for both teams.  Inside a team the 32x32x16 MFMA work of a tile is cut
+// differently for the two products:
+//  * S^T = K Q^T: wave w takes 32 keys (w & 1) x 32 rows (w >> 1), so it keeps
+//    the Q fragments of only 32 rows in registers;
+//  * O^T += V^T P^T: wave w takes DH/4 head dims x all 64 rows.
+// The probabilities go through LDS between the two (8 KB per team and tile).
+// A K, V^T or P fragment read feeds 32 rows instead of 16: 256 KB of LDS
+// reads per tile and 128 rows, against 512 KB when every wave reads the whole
+// tile for 16 rows of its own, which bounded that kernel.
+//
+// The teams run half a tile apart (every SIMD holds one wave of each): while
+// one issues its MFMAs (P.V of tile t-1, then the scores of tile t), the
+// other takes its softmax, so the matrix cores and the VALU work at once.
+// Workgroup barriers separate the half tiles:
+//   interval 2t:    team 0 MFMA(t)     team 1 softmax(t-1)
+//   interval 2t+1:  team 0 softmax(t)  team 1 MFMA(t)
+// with MFMA(t) = { P.V(t-1), S(t) and its row maxima }.  K(t) is read in
+// intervals 2t and 2t+1, V(t) in 2t+2 and 2t+3; so in interval 2t every wave
+// issues its share of the copies of K(t+1) and V(t) into the buffers that
+// K(t-1) and V(t-2) left, and waits for them before the barrier that ends
+// interval 2t+1.  Every LDS access of an interval is complete before the
+// barrier that ends it.
+//
+// One tile of 128 rows takes 1.9 us (38 tiles per workgroup, 64 workgroups:
+// 79 us; MFMAs alone 0.85 us at 2.4 GHz): without the copies 66 us, without the
+// fragment reads 71, without the exponentials or the MFMAs unchanged, so what
+// remains is the chain of barriers and LDS latencies of each half tile.
+//
+// Q reaches the registers through LDS as well (copied into the V^T buffers
+// before the first V^T tile): fetched as MFMA fragments straight from global
+// memory, one CU draws 38 GB/s, through global_load_lds 134-150 GB/s.  The
+// result leaves through LDS for the same reason, as whole rows.
+// ---------------------------------------------------------------------------
+// chunk swizzle of a 128-byte row (V^T, P): 16 consecutive rows put the same
+// chunk into distinct 16-byte bank slots (K, Q and output rows: r & 15)
+#define RFX_VSWZ(r) (((r) & 7) ^ (((r) >> 3) & 1))
+
+RFX_DEV float xmax32(float v) {
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+RFX_DEV float xsum32(float v) {
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+template <int DH>
+__global__ __launch_bounds__(512) void attn_team_kernel(AttnArgs p) {
+  using T = bf16_t;
+  constexpr int NKS = DH / 16;            // 16-wide d steps of S^T
+  constexpr int KRB = DH * 2;             // bytes per K (and Q, and output) row in LDS
+  constexpr int KCH = DH / 8;             // 16-byte chunks per K row
+  constexpr int VRB = AKT * 2;            // bytes per V^T row (128)
+  constexpr int KBYTES = AKT * KRB;
+  constexpr int VBYTES = DH * VRB;
+  constexpr int PBYTES = 64 * VRB;        // P of one team: 64 rows x 64 keys
+  constexpr int NIK = KBYTES / 1024 / 8;  // 1-KB copies per wave and tile, K
+  constexpr int NIV = VBYTES / 1024 / 8;  // same for V^T
+  constexpr int NIQ = 128 * KRB / 1024 / 8;  // same for the 128 Q rows
+  constexpr int NDW = DH / 128;           // 32-wide d blocks of a wave's P.V
+  static_assert(DH == 128 || DH == 256, "a wave's P.V covers DH / 4 = 32 or 64 head dims");
+  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * KBYTES + 2 * VBYTES + 2 * PBYTES];
+  __shared__ float xm[2][2][64];  // [team][key half][row]: row maxima, at the end row sums
+  unsigned char* const kb = smem;
+  unsigned char* const vb = smem + 2 * KBYTES;
+
+  int group, rb;
+  const int nrg = p.rows_pad / 128;
+  if (!attn_decode(blockIdx.x, p.B * p.nsplit, nrg, group, rb)) return;
+  const int b = group / p.nsplit, split = group - b * p.nsplit;
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r32 = lane & 31, h = lane >> 5;
+  const int team = wave >> 2, tw = wave & 3;
+  const int T_ = p.T, Hq = p.Hq;
+  const int nrows = T_ * Hq;
+  // the 32-row blocks of an env are spread evenly over its workgroups, those
+  // of a workgroup over its teams (408 rows: 4, 3, 3 and 3 blocks)
+  const int nb32 = (nrows + 31) / 32;
+  const int nbase = nb32 / nrg, nextra = nb32 - nbase * nrg;
+  const int nbw = nbase + (rb < nextra ? 1 : 0);
+  const int wrow0 = 32 * (rb * nbase + min(rb, nextra));  // first row of the workgroup
+  const int wrows = min(nbw * 32, nrows - wrow0);
+  const int nb0 = (nbw + 1) >> 1;
+  const int nbt = team == 0 ? nb0 : nbw - nb0;  // 32-row blocks of this team (0, 1 or 2)
+  const int trow = team * nb0 * 32;             // its first row within the workgroup
+
+  const int Lc = p.static_len + (*p.n_valid) * p.frame_tokens;
+  const int hole = __builtin_amdgcn_readfirstlane(*p.hole_row), skip = p.frame_tokens;
+  const int n_ct = (Lc + AKT - 1) / AKT;
+  const int n_dt = (T_ + AKT - 1) / AKT;
+  const int total = n_ct + n_dt;
+  const int per = (total + p.nsplit - 1) / p.nsplit;
+  const int t_beg = split * per;
+  const int n = min(total, t_beg + per) - t_beg;
+
+  const T* ck = reinterpret_cast<const T*>(p.cache_k) + (int64_t)b * p.ck_bstride;
+  const T* cvt = reinterpret_cast<const T*>(p.cache_vt) + (int64_t)b * p.ck_bstride;
+  const T* kdb = reinterpret_cast<const T*>(p.kd) + (int64_t)b * T_ * DH;
+  const T* vdb = reinterpret_cast<const T*>(p.vdt) + (int64_t)b * DH * p.tpad;
+  const float scale = rsqrtf((float)DH) * 1.4426950408889634f;
+  const int tpad = p.tpad, Rrow = p.R;  // copied: a lambda must not capture the kernel argument
+  constexpr int RPI = 64 / KCH;         // K rows per copy instruction
+
+  // the lane id, opaque to the compiler: per-lane addresses are rebuilt from it
+  // in every phase instead of being kept in registers (a spill's reload would
+  // wait for the copies in flight)
+  auto fresh_lane = [&]() __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    return ln;
+  };
+  // copy j of this wave's share of tile t (addresses clamped to valid rows;
+  // masked keys get probability zero)
+  auto copy_k = [&](int t, int j) __attribute__((always_inline)) {
+    const int ln = fresh_lane();
+    unsigned char* dst = kb + (t & 1) * KBYTES;
+    t = min(t, n - 1) + t_beg;
+    const bool dyn = t >= n_ct;
+    const int base = dyn ? (t - n_ct) * AKT : t * AKT;
+    const int last = (dyn ? T_ : Lc) - 1;
+    const int hl = dyn ? 0x7fffffff : hole;
+    const T* src = dyn ? kdb : ck;
+    const int kl = ln % KCH, kr = ln / KCH;
+    const int row = RPI * (wave * NIK + j) + kr;
+    int r = min(base + row, last);
+    r += r >= hl ? skip : 0;
+    lds_dma16(src + (int64_t)r * DH + (kl ^ (row & 15)) * 8, dst + (wave * NIK + j) * 1024);
+  };
+  auto copy_v = [&](int t, int j) __attribute__((always_inline)) {
+    const int ln = fresh_lane();
+    unsigned char* dst = vb + (t & 1) * VBYTES;
+    t += t_beg;
+    const bool dyn = t >= n_ct;
+    const int base = dyn ? (t - n_ct) * AKT : t * AKT;
+    const int last = dyn ? 0x7fffffff : Lc - 1;  // dynamic values: zeros up to tpad
+    const int hl = dyn ? 0x7fffffff : hole;
+    const T* src = dyn ? vdb : cvt;
+    const int stride = dyn ? tpad : Rrow;
+    const int vd = ln >> 3, vc = ln & 7;
+    const int d = (wave * NIV + j) * 8 + vd;
+    int key = base + (vc ^ RFX_VSWZ(d)) * 8;
+    key = key <= last ? key : 0;
+    key += key >= hl ? skip : 0;
+    lds_dma16(src + (int64_t)d * stride + key, dst + (wave * NIV + j) * 1024);
+  };
+  // Most tiles are 64 whole cached rows in one piece: their copies then need
+  // only a uniform base and the lane's offset within a tile, kept in
+  // registers.  (The address arithmetic of the general form, clamps, the
+  // spare slot and 64-bit products, was more than a third of the kernel's
+  // VALU work, which bounds it.)  A tile across the spare slot's edge, one
+  // that ends with the cached rows and the dynamic tiles take the general form.
+  uint32_t koffg[NIK], voffg[2];
+#pragma unroll
+  for (int j = 0; j < NIK; ++j) {
+    const int row = RPI * (wave * NIK + j) + lane / KCH;
+    koffg[j] = row * KRB + ((lane % KCH) ^ (row & 15)) * 16;
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {  // rows d of copy j: the swizzle depends on d / 8 only by its parity
+    const int d = (wave * NIV + j) * 8 + (lane >> 3);
+    voffg[j] = (uint32_t)((wave * NIV) * 8 + (lane >> 3)) * (uint32_t)(Rrow * 2) + ((lane & 7) ^ RFX_VSWZ(d)) * 16;
+  }
+  const bool small = (int64_t)DH * Rrow * 2 < (int64_t)1 << 31;  // lane offsets fit 32 bits
+  struct Tile { int t, row; bool whole; };  // row: first physical row (column) of a whole tile
+  auto tile_of = [&](int t) __attribute__((always_inline)) {
+    const int base = (t + t_beg) * AKT;
+    Tile r;
+    r.t = t;
+    r.whole = small && t < n && base + AKT <= Lc && (base >= hole || base + AKT <= hole);
+    r.row = base + (base >= hole ? skip : 0);
+    return r;
+  };
+  // slot i (0 .. 7) of the copies a wave issues in half tiles 2t and 2t + 1:
+  // K(t + 1), then V(t).  One CU takes 16 to 18 cycles per copy (56 to 64
+  // bytes a cycle), and a wave that runs ahead of that stands still: the slots
+  // are spread over the phase's math.  Past the last tile K(n - 1) is copied
+  // again (into the buffer nobody reads), so the count stays the same.
+  auto slot = [&](const Tile& tk, const Tile& tv, int i) __attribute__((always_inline)) {
+    if (i < NIK) {
+      if (tk.whole)
+        lds_dma16(ck + (int64_t)tk.row * DH, koffg[i], kb + (tk.t & 1) * KBYTES + (wave * NIK + i) * 1024);
+      else
+        copy_k(tk.t, i);
+    } else if (i < NIK + NIV) {
+      const int j = i - NIK;
+      if (tv.whole)
+        lds_dma16(cvt + (tv.row + (int64_t)(8 * j) * Rrow), voffg[j & 1], vb + (tv.t & 1) * VBYTES + (wave * NIV + j) * 1024);
+      else
+        copy_v(tv.t, j);
+    }
+  };
+  // end of an interval: LDS accesses complete (and this wave's copies, if
+  // asked), then the barrier
+  auto bar = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  auto bar_vm = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  };
+
+  // ---- Q: 128 rows through the V^T buffers ---------------------------------
+  const int kh = tw & 1, rbS = tw >> 1;
+  const bool s_on = rbS < nbt;
+  const int srow = trow + rbS * 32 + r32;       // this lane's row of S within the workgroup
+  const int rq = wrow0 + srow;
+  const int iq = s_on && rq < nrows ? rq / Hq : 0;
+  uint4 qf[NKS];
+  {
+    const T* qb = reinterpret_cast<const T*>(p.q) + (int64_t)b * p.rows_pad * DH;
+    const int kl = lane % KCH, kr = lane / KCH;
+#pragma unroll
+    for (int j = 0; j < NIQ; ++j) {
+      const int row = RPI * (wave * NIQ + j) + kr;
+      // rows past the valid range compute on row 0's data and are never stored
+      const int r = row < wrows ? wrow0 + row : 0;
+      lds_dma16(qb + (int64_t)r * DH + (kl ^ (row & 15)) * 8, vb + (wave * NIQ + j) * 1024);
+    }
+    if (n > 0) {
+#pragma unroll
+      for (int j = 0; j < NIK; ++j) copy_k(0, j);
+    }
+    bar_vm();
+    const int row = s_on ? srow : r32;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+      qf[ks] = *reinterpret_cast<const uint4*>(vb + row * KRB + ((2 * ks + h) ^ (row & 15)) * 16);
+    bar();
+  }
+
+  f32x16_v o[NDW][2];
+#pragma unroll
+  for (int a = 0; a < NDW; ++a)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) o[a][c] = f32x16_v{};
+  // running maxima of the rows of both 32-row blocks (kept alike by the four
+  // waves), row sums of this lane's own keys
+  float m_run[2] = {-INFINITY, -INFINITY}, l_own = 0.f;
+  f32x16_v s;
+
+  const int db0 = tw * NDW;  // first 32-wide d block of this wave's P.V
+  unsigned char* const pb = smem + 2 * KBYTES + 2 * VBYTES + team * PBYTES;
+
+  // LDS byte offsets of this lane's fragments (toggled between the two
+  // buffers by an XOR): chunk 2ks + h of a row sits at (2ks) ^ (h ^ swizzle)
+  constexpr int NKO = 8;  // the low four bits of a chunk repeat every 8 k-steps
+  uint32_t ko[NKO], vo[4], po[4];
+#pragma unroll
+  for (int i = 0; i < NKO; ++i)
+    ko[i] = (kh * 32 + r32) * KRB + ((2 * i) ^ (h ^ (r32 & 15))) * 16;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t c = ((2 * i) ^ (h ^ RFX_VSWZ(r32))) * 16;
+    vo[i] = 2 * KBYTES + (db0 * 32 + r32) * VRB + c;
+    po[i] = 2 * KBYTES + 2 * VBYTES + team * PBYTES + r32 * VRB + c;
+  }
+  // MFMA(t): P.V of tile t - 1 (if any), then S(t) of this wave's 32 keys x 32
+  // rows (two accumulation chains) and the row maxima of its keys, scaled to
+  // log2 units.  One wave per SIMD issues MFMAs at a time, so nothing else
+  // covers its LDS latency: the fragments of P.V are requested three k-steps
+  // ahead, the K fragments of S KA ahead, the first of them under P.V's MFMAs
+  // (the fences keep the compiler from sinking the reads).  CP: with the
+  // copies of this half tile.
+  auto fence = [&]() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
+  using Zero = std::integral_constant<int, 0>;
+  using One = std::integral_constant<int, 1>;
+  auto mfma_phase = [&](int t, auto PV, auto SC, auto CP) __attribute__((always_inline)) {
+    constexpr int KA = 8;  // K fragments in flight
+    Tile tk, tv;
+    if constexpr (decltype(CP)::value) {
+      tk = tile_of(t + 1);
+      tv = tile_of(t);
+    }
+    auto cslot = [&](int i) __attribute__((always_inline)) {
+      if constexpr (decltype(CP)::value) slot(tk, tv, i);
+    };
+    uint4 kf[KA];
+    auto kloads = [&](int k0, int k1) __attribute__((always_inline)) {
+      if constexpr (decltype(SC)::value) {
+#pragma unroll
+        for (int ks = k0; ks < k1; ++ks)
+          kf[ks % KA] = *reinterpret_cast<const uint4*>(smem + ko[ks % NKO] + (ks / NKO) * 256);
+      }
+    };
+    if constexpr (decltype(PV)::value) {
+      uint4 vf[4][NDW], pf[4][2];
+      auto pv_load = [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) pf[ks][c] = *reinterpret_cast<const uint4*>(smem + po[ks] + c * 32 * VRB);
+#pragma unroll
+        for (int a = 0; a < NDW; ++a) vf[ks][a] = *reinterpret_cast<const uint4*>(smem + vo[ks] + a * 32 * VRB);
+        vo[ks] ^= VBYTES;
+      };
+      auto pv_mfma = [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < NDW; ++a)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) mfma32_step(o[a][c], vf[ks][a], pf[ks][c]);
+      };
+#pragma unroll
+      for (int ks = 0; ks < 3; ++ks) pv_load(ks);
+      fence();
+      pv_mfma(0);
+      fence();
+      pv_load(3);
+      cslot(0);
+      fence();
+      pv_mfma(1);
+      fence();
+      kloads(0, KA / 4);
+      cslot(1);
+      fence();
+      pv_mfma(2);
+      fence();
+      kloads(KA / 4, KA / 2);
+      cslot(2);
+      fence();
+      pv_mfma(3);
+      cslot(3);
+      fence();
+    } else {
+      kloads(0, KA / 2);
+    }
+    if constexpr (decltype(SC)::value) {
+      kloads(KA / 2, KA);
+      fence();
+      f32x16_v s1 = f32x16_v{};
+      s = f32x16_v{};
+#pragma unroll
+      for (int ks = 0; ks < NKS; ks += 2) {
+        mfma32_step(s, kf[ks % KA], qf[ks]);
+        mfma32_step(s1, kf[(ks + 1) % KA], qf[ks + 1]);
+        fence();
+        if (ks + KA < NKS) kloads(ks + KA, ks + KA + 2);
+        if (ks % 4 == 2) cslot(4 + ks / 4);
+        fence();
+      }
+#pragma unroll
+      for (int i = 0; i < NKO; ++i) ko[i] ^= KBYTES;
+      s += s1;
+    }
+  };
+  auto row_max = [&](int t) __attribute__((always_inline)) {
+    if (!s_on) return;
+    const int ln = fresh_lane(), r32 = ln & 31, h = ln >> 5;
+    // lane (r32, h), value q: key 32 kh + 8 (q >> 2) + 4 h + (q & 3) of the tile
+    const int tt = t + t_beg;
+    const bool dyn = tt >= n_ct;
+    if (dyn || (tt + 1) * AKT > Lc) {
+      const int lim = (dyn ? (iq > 0 ? T_ : 1) - (tt - n_ct) * AKT : Lc - tt * AKT) - 32 * kh - 4 * h;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) s[q] = 8 * (q >> 2) + (q & 3) < lim ? s[q] : -INFINITY;
+    }
+    float mt = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) mt = fmaxf(mt, s[q]);
+    mt = xmax32(mt) * scale;
+    if (h == 0) xm[team][kh][rbS * 32 + r32] = mt;
+  };
+  // softmax(t): probabilities of this wave's S against the running maxima as
+  // they stand, while the tile's row maxima arrive from LDS.  The maxima are
+  // lazy: they move only when a row's tile max exceeds them by more than 8
+  // (log2 units), so the probabilities stay below 2^8 and a move is rare; then
+  // O is rescaled and the probabilities are taken again.  All four waves of a
+  // team see the same maxima and keep the same running ones.
+  auto softmax = [&](int t, auto CP) __attribute__((always_inline)) {
+    Tile tk, tv;
+    if constexpr (decltype(CP)::value) {
+      tk = tile_of(t + 2);
+      tv = tile_of(t + 1);
+    }
+    auto cslot = [&](int i) __attribute__((always_inline)) {
+      if constexpr (decltype(CP)::value) slot(tk, tv, i);
+    };
+    const int ln = fresh_lane(), r32 = ln & 31, h = ln >> 5;
+    const int vswz = RFX_VSWZ(r32);
+    const float x0 = xm[team][0][r32], x1 = xm[team][1][r32];
+    const float x2 = xm[team][0][32 + r32], x3 = xm[team][1][32 + r32];
+    cslot(0);
+    cslot(1);
+    float e[16], psum = 0.f;
+    auto expo = [&](int q0, int q1) __attribute__((always_inline)) {
+      const float m = rbS ? m_run[1] : m_run[0];
+      const float m_use = m == -INFINITY ? 0.f : m;
+#pragma unroll
+      for (int q = q0; q < q1; ++q) {
+        e[q] = __builtin_amdgcn_exp2f(s[q] * scale - m_use);  // arguments at most 8
+        psum += e[q];
+      }
+    };
+    expo(0, 4);
+    cslot(2);
+    expo(4, 8);
+    cslot(3);
+    expo(8, 12);
+    cslot(4);
+    expo(12, 16);
+    cslot(5);
+    const float mt[2] = {fmaxf(x0, x1), fmaxf(x2, x3)};
+    if (__any((nbt > 0 && mt[0] > m_run[0] + 8.f) || (nbt > 1 && mt[1] > m_run[1] + 8.f))) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        if (c < nbt && __any(mt[c] > m_run[c] + 8.f)) {
+          const float m_new = fmaxf(m_run[c], mt[c]);
+          const float corr = m_new == -INFINITY ? 1.f : exp2f(m_run[c] - m_new);
+          m_run[c] = m_new;
+          if (rbS == c) l_own *= corr;
+#pragma unroll
+          for (int a = 0; a < NDW; ++a) o[a][c] *= corr;
+        }
+      }
+      psum = 0.f;
+      expo(0, 16);
+    }
+    l_own += psum;
+    cslot(6);
+    const int prow = rbS * 32 + r32;
+    if (s_on) {
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *reinterpret_cast<uint2*>(pb + prow * VRB + ((4 * kh + q4) ^ vswz) * 16 + h * 8) =
+            make_uint2(pack_bf16x2(e[4 * q4], e[4 * q4 + 1]), pack_bf16x2(e[4 * q4 + 2], e[4 * q4 + 3]));
+    }
+    cslot(7);
+  };
+
+  auto mfma = [&](int t, auto PV, auto SC, auto CP) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(1);
+    mfma_phase(t, PV, SC, CP);
+    __builtin_amdgcn_s_setprio(0);
+    if constexpr (decltype(SC)::value) row_max(t);
+  };
+  if (n > 0) {
+    const Tile t1 = tile_of(1), t0 = tile_of(0);
+    if (n > 1) {
+#pragma unroll
+      for (int i = 0; i < NIK; ++i) slot(t1, t0, i);
+    }
+#pragma unroll
+    for (int i = NIK; i < NIK + NIV; ++i) slot(t1, t0, i);
+    // (one loop per team with the ends peeled: a branch around P.V in the
+    // loop would cost a second copy of O in registers)
+    if (team == 0) {
+      mfma(0, Zero{}, One{}, Zero{});
+      bar();
+      softmax(0, Zero{});
+      bar_vm();
+      for (int t = 1; t < n; ++t) {
+        mfma(t, One{}, One{}, One{});
+        bar();
+        softmax(t, Zero{});
+        bar_vm();
+      }
+      mfma(n, One{}, Zero{}, Zero{});
+      bar();
+    } else {
+      bar();
+      mfma(0, Zero{}, One{}, Zero{});
+      bar_vm();
+      for (int t = 1; t < n; ++t) {
+        softmax(t - 1, One{});
+        bar();
+        mfma(t, One{}, One{}, Zero{});
+        bar_vm();
+      }
+      softmax(n - 1, Zero{});
+      bar();
+      mfma(n, One{}, Zero{}, Zero{});
+    }
+  }
+
+  // ---- results through LDS -------------------------------------------------
+  // (the barrier below also ends every read of the K buffers, which the output
+  // rows reuse: 128 rows of KRB bytes)
+  if (s_on) {
+    const float l = xsum32(l_own);
+    if (h == 0) xm[team][kh][rbS * 32 + r32] = l;
+  }
+  bar();
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (c < nbt) {
+      const int row = trow + c * 32 + r32;  // within the workgroup
+      const float l = xm[team][0][c * 32 + r32] + xm[team][1][c * 32 + r32];
+      const float f = p.nsplit == 1 ? (l > 0.f ? 1.f / l : 0.f) : 1.f;
+#pragma unroll
+      for (int a = 0; a < NDW; ++a)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          *reinterpret_cast<uint2*>(kb + row * KRB + (((db0 + a) * 4 + q4) ^ (row & 15)) * 16 + h * 8) =
+              make_uint2(pack_bf16x2(o[a][c][4 * q4] * f, o[a][c][4 * q4 + 1] * f),
+                         pack_bf16x2(o[a][c][4 * q4 + 2] * f, o[a][c][4 * q4 + 3] * f));
+      if (p.nsplit > 1 && tw == 0 && h == 0 && wrow0 + row < nrows) {
+        const int64_t prow = ((int64_t)b * p.nsplit + split) * p.rows_pad + wrow0 + row;
+        *reinterpret_cast<float2*>(p.part_ml + prow * 2) = make_float2(m_run[c], l);
+      }
+    }
+  }
+  bar();
+  T* const dst = p.nsplit == 1 ? reinterpret_cast<T*>(p.out) + ((int64_t)b * nrows + wrow0) * DH
+                               : reinterpret_cast<T*>(p.part_o) +
+                                     (((int64_t)b * p.nsplit + split) * p.rows_pad + wrow0) * DH;
+  for (int e = threadIdx.x; e < wrows * KCH; e += 512) {
+    const int row = e / KCH, c = e % KCH;
+    st16(dst + (int64_t)row * DH + c * 8,
+         *reinterpret_cast<const uint4*>(kb + row * KRB + (c ^ (row & 15)) * 16));
+  }
+}
+
 // Merge the key splits: o = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s,
 // splits combined in index order.  One thread per (query row, VEC
 // consecutive d): 16-byte accesses (8 bf16 or 4 fp32 values) when the grid
 // still holds a wave of blocks, else 4-byte ones (2 bf16) for four times the
 // blocks at a few envs (one env: 3.45 -> 3.13 us against 8-byte ones).
 // The partial O_s are fp32 on the fp32 path and bf16 on the bf16 path.
-constexpr int kMaxSplits = 16;
+constexpr int kMaxSplits = 16;      // most splits attn_merge_kernel takes
+constexpr int kMaxTeamSplits = 64;  // most splits of the team kernel
 
 // MAXS: the split count it is compiled for (at least p.nsplit): the partials
 // of every split are held in registers at once, so a bound of 16 for two
@@ -1313,35 +1833,120 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs p) {
   *reinterpret_cast<Raw*>(dst) = outw;
 }
 
+// The same for many splits (the team kernel's, up to 64): a row's splits are
+// dealt to eight groups of threads, 16 bytes per load, so a thread has at most
+// eight partials in flight and a row one memory round trip; the groups' sums
+// meet in LDS.  One env, 61 splits of 408 rows (12.7 MB of partials): 20.0 us
+// with all splits walked by one thread per two values.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_merge_wide_kernel(AttnArgs p) {
+  using T = bf16_t;
+  constexpr int G = 8, PT = kMaxTeamSplits / G;  // groups; partials per thread
+  constexpr int CPR = DH / 8;                    // 16-byte chunks per row
+  constexpr int RPB = 256 / (CPR * G);           // rows per block
+  __shared__ __attribute__((aligned(16))) float accs[RPB][G][DH + 4];
+  __shared__ float2 mls[RPB][G];
+  const int b = blockIdx.y;
+  const int rsub = threadIdx.x / (CPR * G), g = threadIdx.x / CPR % G, c = threadIdx.x % CPR;
+  const int rq = blockIdx.x * RPB + rsub, nrows = p.T * p.Hq;
+  const int rl = min(rq, nrows - 1);  // rows past the end: any valid row, never stored
+  const int64_t base = (int64_t)b * p.nsplit * p.rows_pad + rl;
+  float2 ml[PT];
+  uint4 raw[PT];
+#pragma unroll
+  for (int i = 0; i < PT; ++i) {
+    const int sp = g + i * G;
+    if (sp < p.nsplit) {
+      const int64_t prow = base + (int64_t)sp * p.rows_pad;
+      ml[i] = *reinterpret_cast<const float2*>(p.part_ml + prow * 2);
+      raw[i] = ld16(reinterpret_cast<const T*>(p.part_o) + prow * DH + c * 8);
+    }
+  }
+  float M = -INFINITY, L = 0.f;
+#pragma unroll
+  for (int i = 0; i < PT; ++i)
+    if (g + i * G < p.nsplit) M = fmaxf(M, ml[i].x);
+  const float Mu = M == -INFINITY ? 0.f : M;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < PT; ++i)
+    if (g + i * G < p.nsplit) {
+      const float w = exp2f(ml[i].x - Mu);
+      float v[8];
+      frag_to_f(raw[i], v, T());
+      L += w * ml[i].y;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += w * v[e];
+    }
+  float* dst = &accs[rsub][g][c * 8];
+  *reinterpret_cast<float4*>(dst) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+  *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  if (c == 0) mls[rsub][g] = make_float2(M, L);
+  __syncthreads();
+  // two consecutive d per thread, the groups in order
+  for (int e = threadIdx.x; e < RPB * DH / 2; e += 256) {
+    const int r = e / (DH / 2), d = (e % (DH / 2)) * 2;
+    if (blockIdx.x * RPB + r >= nrows) continue;
+    float Ma = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < G; ++i) Ma = fmaxf(Ma, mls[r][i].x);
+    const float Mau = Ma == -INFINITY ? 0.f : Ma;
+    float La = 0.f, x = 0.f, y = 0.f;
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const float2 q = mls[r][i];
+      const float w = exp2f(q.x - Mau);
+      La += w * q.y;
+      x += w * accs[r][i][d];
+      y += w * accs[r][i][d + 1];
+    }
+    const float inv = La > 0.f ? 1.f / La : 0.f;
+    T* o = reinterpret_cast<T*>(p.out) + ((int64_t)b * nrows + blockIdx.x * RPB + r) * DH + d;
+    *reinterpret_cast<uint32_t*>(o) = pack_bf16x2(x * inv, y * inv);
+  }
+}
+
 // Query rows per attention workgroup: 128 on the bf16 path, 64 on fp32.
 int attention_rows_per_block(int elem_bytes) { return elem_bytes == 2 ? 128 : 64; }
 
 // Kernel and key-split count for (B envs, rows query rows, up to max_keys
-// cached keys).  One workgroup per CU is resident (LDS bound), so both aim
-// for about one wave of workgroups over the 256 CUs.  The 16-row variants
-// cover 128 rows per workgroup; when that grid would reach one key tile per
-// split (a few envs, short context) the launch is latency-bound and the
-// wave-pair variant (32 rows per workgroup, one tile per split) is used,
-// otherwise the software-pipelined 16-row kernel.  `force` (ATTN_AUTO,
-// ATTN_ROWS16, ATTN_PAIR or ATTN_ROWS16_PIPE) overrides the choice.
-AttnPlan attention_plan(int B, int rows, int max_keys, int elem_bytes, int force) {
+// cached keys).  One workgroup per CU is resident (LDS bound), so all aim for
+// about one wave of workgroups over the 256 CUs.  `base` is the count of
+// 128-row workgroups without a key split.
+//  * one tile per workgroup within one wave as wave pairs (32 rows each): the
+//    launch is latency-bound and the pair kernel's (one env, 816 cached keys:
+//    10.4 us with the merge against 11.2 us with teams);
+//  * else base < 16 (more than 16 key splits fill the chip), heads of 128 or
+//    256: the team kernel, up to 64 splits.  With the merge, against the
+//    former limit of 16 splits: one env with 3,888 / 15,408 / 38,448 cached
+//    keys 19.5 -> 15.5, 41.5 -> 22.5, 88.5 -> 35.4 us; 101 tokens 27.0 -> 15.0;
+//    two envs 24.6 -> 14.8 us.  At base 16 (four envs) both take 17.7 us;
+//  * else the 16-row waves, software-pipelined (32 envs 44.7 us against 46.3).
+// `force` (ATTN_ROWS16, ATTN_PAIR or ATTN_ROWS16_PIPE) overrides the choice.
+AttnPlan attention_plan(int B, int rows, int head_dim, int max_keys, int elem_bytes, int force) {
   const int tiles = (max_keys + AKT - 1) / AKT + 1;
   AttnPlan pl;
   pl.kernel = ATTN_ROWS16;
   const int rpb = attention_rows_per_block(elem_bytes);
   int base = B * ((rows + rpb - 1) / rpb);
+  int most = kMaxSplits;
   if (elem_bytes == 2) {
+    const int pairs = B * ((rows + 31) / 32);
     const bool latency = 256 / base >= tiles;
-    if (force == ATTN_PAIR || (force == ATTN_AUTO && latency)) {
+    const bool teams = force == ATTN_AUTO && head_dim >= 128 && base < 16;
+    if (teams && pairs * tiles > 256) {
+      pl.kernel = ATTN_TEAM;
+      most = kMaxTeamSplits;
+    } else if (force == ATTN_PAIR || (force == ATTN_AUTO && latency)) {
       pl.kernel = ATTN_PAIR;
-      base = B * ((rows + 31) / 32);
+      base = pairs;
     } else if (force != ATTN_ROWS16) {
       pl.kernel = ATTN_ROWS16_PIPE;
     }
   }
   int s = 256 / base;
   if (s > tiles) s = tiles;
-  if (s > kMaxSplits) s = kMaxSplits;
+  if (s > most) s = most;
   pl.splits = s < 1 ? 1 : s;
   return pl;
 }
@@ -1352,6 +1957,12 @@ static void launch_attn_dh(const AttnArgs& a, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
     const int rows = a.T * a.Hq;
     const int g8 = ((groups + 7) / 8) * 8;
+    if constexpr (DH >= 128) {
+      if (a.kernel == ATTN_TEAM) {
+        RFX_LAUNCH((attn_team_kernel<DH>), dim3(g8 * (a.rows_pad / 128)), dim3(512), 0, s, a);
+        return;
+      }
+    }
     if (a.kernel == ATTN_PAIR)
       RFX_LAUNCH((attn_pair_kernel<DH>), dim3(g8 * ((rows + 31) / 32)), dim3(128), 0, s, a);
     else if (a.kernel == ATTN_ROWS16_PIPE)
@@ -1381,6 +1992,14 @@ static void launch_merge_dh(const AttnArgs& a, hipStream_t s) {
   constexpr int V16 = 16 / (int)sizeof(T);
   constexpr int RPB16 = 256 / (DH / V16);
   const int rows = a.T * a.Hq;
+  if constexpr (sizeof(T) == 2) {
+    // (from nine splits on: one env, 14 splits 3.4 -> 2.9 us, 26 splits 7.7 -> 3.8)
+    if (a.nsplit > 8) {
+      constexpr int RPB = 256 / DH;
+      RFX_LAUNCH((attn_merge_wide_kernel<DH>), dim3((rows + RPB - 1) / RPB, a.B), dim3(256), 0, s, a);
+      return;
+    }
+  }
   const int blocks16 = (rows + RPB16 - 1) / RPB16 * a.B;
   if (sizeof(T) == 4 || blocks16 >= 256) {
     launch_merge_vec<T, DH, V16>(a, dim3((rows + RPB16 - 1) / RPB16, a.B), s);
@@ -1392,8 +2011,10 @@ static void launch_merge_dh(const AttnArgs& a, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_attention(const AttnArgs& a, int head_dim, hipStream_t s) {
-  if (a.nsplit < 1 || a.nsplit > kMaxSplits || a.rows_pad % 128) return hipErrorInvalidValue;
-  if (a.kernel != ATTN_ROWS16 && a.kernel != ATTN_PAIR && a.kernel != ATTN_ROWS16_PIPE) return hipErrorInvalidValue;
+  if (a.nsplit < 1 || a.nsplit > (a.kernel == ATTN_TEAM ? kMaxTeamSplits : kMaxSplits) || a.rows_pad % 128)
+    return hipErrorInvalidValue;
+  if (a.kernel < ATTN_ROWS16 || a.kernel > ATTN_TEAM || (a.kernel == ATTN_TEAM && (head_dim < 128 || sizeof(T) != 2)))
+    return hipErrorInvalidValue;
   switch (head_dim) {
     case 64: launch_attn_dh<T, 64>(a, s); break;
     case 128: launch_attn_dh<T, 128>(a, s); break;

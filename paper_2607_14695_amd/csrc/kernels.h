@@ -101,14 +101,16 @@ template <typename T> hipError_t launch_attention(const AttnArgs& a, int head_di
 template <typename T> hipError_t launch_attn_merge(const AttnArgs& a, int head_dim, hipStream_t s);
 int attention_rows_per_block(int elem_bytes);
 // bf16 attention kernels: 16-row waves (128 rows per workgroup; plain or
-// software-pipelined, equal bit for bit) or one wave pair per workgroup (32
-// rows); ATTN_AUTO picks by the launch geometry
-enum AttnKernel : int { ATTN_AUTO = 0, ATTN_ROWS16 = 1, ATTN_PAIR = 2, ATTN_ROWS16_PIPE = 3 };
+// software-pipelined, equal bit for bit), one wave pair per workgroup (32
+// rows) or two four-wave teams (128 rows, 64-row teams half a tile apart;
+// heads of 128 and 256); ATTN_AUTO picks by the launch geometry, ATTN_TEAM
+// only through it
+enum AttnKernel : int { ATTN_AUTO = 0, ATTN_ROWS16 = 1, ATTN_PAIR = 2, ATTN_ROWS16_PIPE = 3, ATTN_TEAM = 4 };
 struct AttnPlan {
   int kernel;
   int splits;
 };
-AttnPlan attention_plan(int B, int rows, int max_keys, int elem_bytes, int force);
+AttnPlan attention_plan(int B, int rows, int head_dim, int max_keys, int elem_bytes, int force);
 
 // Precision of the residual stream and of the RMS statistics.  NORM_FP32 is
 // the method (fp32 statistics, Section 3.2); the other two reproduce the

@@ -90,6 +90,12 @@ struct Plan {
   size_t off[kWsParts];
 };
 
+// Bytes of the static device array of the allocation-free entry point.
+constexpr size_t kScratchBytes = size_t(64) << 20;
+// Bytes of it that a chunk of this plan needs: workspace parts 1..16 (the RoPE
+// tables through the split-K partials), laid out as in the workspace.
+size_t static_scratch_bytes(const Plan& P) { return P.off[17] - P.off[1]; }
+
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 SplitK make_split(int M, int K, int splits, int eb) {
@@ -153,7 +159,7 @@ Plan make_plan(const reflex_config* c) {
   p.o = make_split(p.M, c->n_q_heads * c->head_dim,
                    gemm_pick_splits(p.M, c->width, c->n_q_heads * c->head_dim, eb), eb);
   p.down = make_split(p.M, c->mlp_dim, gemm_pick_splits(p.M, c->width, c->mlp_dim, eb), eb);
-  const AttnPlan ap = attention_plan(c->batch, rows, p.R, eb, c->attn_kernel);
+  const AttnPlan ap = attention_plan(c->batch, rows, c->head_dim, p.R, eb, c->attn_kernel);
   p.attn_splits = ap.splits;
   p.attn_kernel = ap.kernel;
   p.max_parts = p.o.splits > p.down.splits ? p.o.splits : p.down.splits;
@@ -175,7 +181,7 @@ Plan make_plan(const reflex_config* c) {
   sz[10] = B * dh * (size_t)p.tpad * eb;                                  // vdt
   sz[11] = 0;  // (unused)
   sz[12] = (size_t)p.M * c->n_q_heads * dh * eb;                          // o
-  sz[13] = B * p.attn_splits * (size_t)p.rows_pad * dh * sizeof(float);   // part_o
+  sz[13] = B * p.attn_splits * (size_t)p.rows_pad * dh * eb;              // part_o (element type: bf16 or fp32)
   sz[14] = B * p.attn_splits * (size_t)p.rows_pad * 2 * sizeof(float);    // part_ml
   sz[15] = (size_t)p.M * c->mlp_dim * eb;                                 // z
   sz[16] = (size_t)p.max_parts * p.M * D * sizeof(float);                 // rparts
@@ -186,12 +192,24 @@ Plan make_plan(const reflex_config* c) {
   sz[19] = L * p.naive_vt_stride;                                         // naive_vt
   sz[20] = (size_t)p.M * (p.Nqkv > 2 * c->mlp_dim ? p.Nqkv : 2 * c->mlp_dim) * sizeof(float);  // uf_wide
   sz[21] = (size_t)p.M * c->action_dim * sizeof(float);                   // uf_v
-  size_t off = 0;
-  for (int i = 0; i < kWsParts; ++i) {
-    p.off[i] = off;
-    off += align256(sz[i]);
+  auto lay_out = [&] {
+    size_t off = 0;
+    for (int i = 0; i < kWsParts; ++i) {
+      p.off[i] = off;
+      off += align256(sz[i]);
+    }
+    p.ws_bytes = off;
+  };
+  lay_out();
+  // more than 16 key splits only while the chunk still fits the static scratch
+  // array of the allocation-free entry point (16 splits always took more bytes
+  // there when partials were sized as fp32)
+  if (p.attn_splits > 16 && static_scratch_bytes(p) > kScratchBytes) {
+    p.attn_splits = 16;
+    sz[13] = B * p.attn_splits * (size_t)p.rows_pad * dh * eb;
+    sz[14] = B * p.attn_splits * (size_t)p.rows_pad * 2 * sizeof(float);
+    lay_out();
   }
-  p.ws_bytes = off;
   return p;
 }
 
@@ -1069,7 +1087,6 @@ int denoise_launch(reflex_ctx* ctx, int mode, const reflex_sources* src, std::ve
 // eagerly (instantiating a graph allocates).  One array per device, shared by
 // every such call on that device.
 // ---------------------------------------------------------------------------
-constexpr size_t kScratchBytes = size_t(64) << 20;
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 void* g_scratch_dev[kMaxDevices];  // device address of `scratch` per device (null until set up)
@@ -1093,10 +1110,6 @@ int scratch_address(void** out) {
   *out = g_scratch_dev[dev];
   return REFLEX_OK;
 }
-
-// Bytes of static scratch a chunk of this context needs: workspace parts 1..16
-// (the RoPE tables through the split-K partials), laid out as in the workspace.
-size_t static_scratch_bytes(const Plan& P) { return P.off[17] - P.off[1]; }
 
 int denoise_launch_static(reflex_ctx* ctx, const float* state, const float* noise, int32_t num_steps,
                           const float* taus, float* actions_out) {
