@@ -609,29 +609,6 @@ RFX_DEV float xsum16_32(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// Copy of 16 bytes per lane from global memory into LDS (global_load_lds,
-// LDS destination from M0), issued through inline assembly: the compiler
-// then does not track these LDS writes and waits for its own LDS reads with
-// partial counts instead of draining every outstanding read first.  Every
-// kernel that uses it orders the copies itself: a vmcnt(0) wait and a
-// barrier come before any read of a stage, and no stage is overwritten
-// before a barrier that follows its last read.  Outstanding copies it does
-// not know of only make the compiler's own vmcnt waits stricter (loads
-// complete in order).  M0 is a reserved register the compiler sets right
-// before each instruction of its own that reads it, so it is not declared
-// clobbered (it cannot be); the kernels using this helper contain no other
-// M0 reader.
-RFX_DEV void lds_dma16(const void* g, void* lds) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :: "v"(g), "s"((unsigned)(size_t)lds) : "memory");
-}
-
-// The same from a wave-uniform base and a 32-bit byte offset per lane.
-RFX_DEV void lds_dma16(const void* base, uint32_t off, void* lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(off), "s"(base), "s"((unsigned)(size_t)lds) : "memory");
-}
-
 template <int DH>
 __global__ __launch_bounds__(512) void attn16p_kernel(AttnArgs p) {
   using T = bf16_t;
@@ -1929,25 +1906,30 @@ AttnPlan attention_plan(int B, int rows, int head_dim, int max_keys, int elem_by
   pl.kernel = ATTN_ROWS16;
   const int rpb = attention_rows_per_block(elem_bytes);
   int base = B * ((rows + rpb - 1) / rpb);
-  int most = kMaxSplits;
+  auto fill = [&](int groups, int most) {
+    int s = 256 / groups;
+    if (s > tiles) s = tiles;
+    if (s > most) s = most;
+    return s < 1 ? 1 : s;
+  };
+  bool teams = false;
+  int groups = base;
   if (elem_bytes == 2) {
     const int pairs = B * ((rows + 31) / 32);
     const bool latency = 256 / base >= tiles;
-    const bool teams = force == ATTN_AUTO && head_dim >= 128 && base < 16;
-    if (teams && pairs * tiles > 256) {
-      pl.kernel = ATTN_TEAM;
-      most = kMaxTeamSplits;
-    } else if (force == ATTN_PAIR || (force == ATTN_AUTO && latency)) {
+    teams = force == ATTN_AUTO && head_dim >= 128 && base < 16 && pairs * tiles > 256;
+    if (force == ATTN_PAIR || (force == ATTN_AUTO && latency)) {
       pl.kernel = ATTN_PAIR;
-      base = pairs;
+      groups = pairs;
     } else if (force != ATTN_ROWS16) {
       pl.kernel = ATTN_ROWS16_PIPE;
     }
   }
-  int s = 256 / base;
-  if (s > tiles) s = tiles;
-  if (s > most) s = most;
-  pl.splits = s < 1 ? 1 : s;
+  pl.few_splits = pl.splits = fill(groups, kMaxSplits);
+  if (teams) {
+    pl.kernel = ATTN_TEAM;
+    pl.splits = fill(base, kMaxTeamSplits);
+  }
   return pl;
 }
 

@@ -97,6 +97,29 @@ RFX_DEV uint4 f_to_frag(const float* in, bf16_t) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// Copy of 16 bytes per lane from global memory into LDS (global_load_lds,
+// LDS destination from M0), issued through inline assembly: the compiler
+// then does not track these LDS writes and waits for its own LDS reads with
+// partial counts instead of draining every outstanding read first.  Every
+// kernel that uses it orders the copies itself: a vmcnt(0) wait and a
+// barrier come before any read of a stage, and no stage is overwritten
+// before a barrier that follows its last read.  Outstanding copies it does
+// not know of only make the compiler's own vmcnt waits stricter (loads
+// complete in order).  M0 is a reserved register the compiler sets right
+// before each instruction of its own that reads it, so it is not declared
+// clobbered (it cannot be); the kernels using this helper contain no other
+// M0 reader.
+RFX_DEV void lds_dma16(const void* g, void* lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :: "v"(g), "s"((unsigned)(size_t)lds) : "memory");
+}
+
+// The same from a wave-uniform base and a 32-bit byte offset per lane.
+RFX_DEV void lds_dma16(const void* base, uint32_t off, void* lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(off), "s"(base), "s"((unsigned)(size_t)lds) : "memory");
+}
+
 RFX_DEV float warp_sum(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);

@@ -15,17 +15,17 @@
 // into the layouts the attention kernel reads.
 //
 // Two regimes:
-//  * gemm_skinny (M <= 64): weight streaming.  At one environment the
-//    activations are 51 rows while every weight byte is read once per Euler
-//    step, so the kernel is bound by HBM bandwidth on the weights.  A workgroup
-//    owns a 32-column strip (or a 16 + 16 paired strip) and a K range; its four
-//    waves interleave k-steps so that, per weight row, the wave group reads 256
-//    contiguous bytes per round; fragments go straight from global memory into
-//    MFMA operands (every weight byte is used by all rows in one instruction).
-//    The waves' partial tiles are summed through LDS.  K may be split across
-//    workgroups for the plain fp32 epilogue; the consumer (the residual/norm
-//    kernel) sums the split partials, so no atomics and no extra launch.
-//  * gemm_tiled (M > 64): 128x128 workgroup tiles, 2x2 waves of 64x64, two
+//  * weight streaming (M <= 128 on the bf16 path, 64 on the fp32 path).  At one
+//    environment the activations are 51 rows while every weight byte is read
+//    once per Euler step.  A workgroup owns a 32-column strip (or a 16 + 16
+//    paired strip) and a K range and all or some of the rows; the waves'
+//    partial tiles are summed through LDS.  K may be split across workgroups
+//    for the plain fp32 epilogue; the consumer (the residual/norm kernel) sums
+//    the split partials, so no atomics and no extra launch.  gemm_stream copies
+//    both operands into LDS (bf16, more than 16 rows), gemm_skinny_lds only the
+//    activations (bf16, up to 16 rows: the conditioning MLPs), gemm_skinny
+//    fetches both as fragments (fp32, or a K range that is no multiple of 32).
+//  * gemm_tiled (more rows): 128x128 workgroup tiles, 2x2 waves of 64x64, two
 //    k-steps (128 bytes of K per row) per LDS stage, double-buffered LDS with
 //    the next stage's global loads in flight during the MFMAs.
 #include "common.h"
@@ -450,7 +450,165 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_lds(GemmArgs p) {
   }
 }
 
-// launch helper for the LDS-staged skinny kernel (bf16, M <= 64)
+// --------------------------------------------------------------------------
+// skinny, bf16, both operands through LDS.  A workgroup owns 16*MB rows, a
+// strip of 32 columns (16 + 16 for the paired epilogues) and a K range, cut
+// into stages of 128 elements (256 bytes of every row); up to NS - 1 stages
+// are in flight.  Every byte reaches LDS by global_load_lds (four rows per
+// instruction): fetched as MFMA fragments (16 rows x 64 bytes, the lanes of a
+// row 16 apart) one CU draws 38 GB/s from its L2, this way 134-150 GB/s, and
+// the weight strip is the larger part of what a workgroup must fetch.  The
+// eight waves take the four 32-wide k-steps of a stage x two halves of the
+// rows; the four partial tiles of a row half are summed through LDS.
+// 16-byte chunks are XOR-swizzled by (row mod 16).  Against the activations
+// in LDS and the weights as fragments, one env (51 rows): output projection
+// 5.7 -> 4.4 us, gate|up 8.3 -> 7.1 (16.8 MB of weights), down 6.6 -> 5.4, QKV
+// 6.4 -> 6.0; against the 128x128 tiles, 101 rows: QKV 11.1 -> 7.0, output
+// projection 7.0 -> 5.3, gate|up 10.1 -> 8.6; a 576-wide expert with 114 rows
+// (K of 576, 640 and 1728, few column tiles): 15.3 -> 4.7, 11.9 -> 3.4,
+// 11.5 -> 5.2, down 23.5 -> 4.5 us.
+// --------------------------------------------------------------------------
+constexpr int SKT = 128;          // K elements per stage
+constexpr int SROWB = SKT * 2;    // bytes per stage row
+constexpr int stream_stage_bytes(int MB) { return (16 * MB + 32) * SROWB; }
+// The conditioning MLPs have several times more strips than CUs: rings small
+// enough for two workgroups per CU (20 rows: 31.1 -> 26.4 us per launch).
+constexpr int stream_stages(int MB, int EPI) {
+  const bool many = EPI == EPI_SILU || EPI == EPI_MOD;
+  return MB <= 2 ? (many ? 4 : 8) : (MB <= 4 ? (many ? 3 : 6) : 4);
+}
+
+template <int MB, int EPI>
+__global__ __launch_bounds__(512) void gemm_stream(GemmArgs p) {
+  using T = bf16_t;
+  constexpr int PAIR = EpiPair<EPI>::value;
+  constexpr int NS = stream_stages(MB, EPI), SB = stream_stage_bytes(MB);
+  constexpr int COLS = PAIR ? 16 : 32;  // first columns per workgroup
+  constexpr int MBW = MB / 2;           // 16-row blocks per wave
+  constexpr int NI = MB / 2 + 1;        // copy instructions per wave and stage
+  constexpr int RCOLS = 33;             // reduction row (padded)
+  static_assert(MB % 2 == 0 && NS * SB <= 160 * 1024, "ring fits LDS");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+  const int ks = wave & 3, mh = wave >> 2;
+  const int z = blockIdx.z;
+  const int mchunk = blockIdx.y / p.splits, split = blockIdx.y % p.splits;
+  const int m0 = mchunk * (16 * MB);
+  int n0, pair_off;
+  if constexpr (PAIR == PAIR_HEAD) {
+    const int half = p.qkv.head_dim >> 1, per_head = half / COLS;
+    const int h = blockIdx.x / per_head;
+    n0 = h * p.qkv.head_dim + (blockIdx.x - h * per_head) * COLS;
+    pair_off = half;
+  } else {
+    n0 = blockIdx.x * COLS;
+    pair_off = p.N;
+  }
+  const int kbeg = split * p.k_per_split;
+  const int klen = min(p.K, kbeg + p.k_per_split) - kbeg;  // a multiple of 32
+  const int nst = (klen + SKT - 1) / SKT;
+
+  const T* A = reinterpret_cast<const T*>(p.A) + (int64_t)z * p.a_bstride + kbeg;
+  const T* B = reinterpret_cast<const T*>(p.B) + (int64_t)z * p.b_bstride + kbeg;
+  // copy i of this wave: stage rows 4u .. 4u + 3, u = wave * NI + i; rows
+  // 0 .. 16 MB - 1 are activations, the 32 after them weights (a copy never
+  // mixes the two).  Rows past M or N repeat the last one: every wave issues
+  // NI copies per stage and can wait on one count.
+  const T* src[NI];
+  int kc[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int row = 4 * (wave * NI + i) + (lane >> 4);
+    kc[i] = ((lane & 15) ^ (row & 15)) * 8;
+    if (4 * (wave * NI + i) < 16 * MB) {
+      src[i] = A + (int64_t)min(m0 + row, p.M - 1) * p.lda;
+    } else {
+      const int w = row - 16 * MB;
+      int brw;
+      if (PAIR == PAIR_NONE) brw = min(n0 + w, p.N - 1);
+      else brw = n0 + (w & 15) + (w >= 16 ? pair_off : 0);
+      src[i] = B + (int64_t)brw * p.ldb;
+    }
+  }
+  auto issue = [&](int st, int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      int k = st * SKT + kc[i];
+      k = k < klen ? k : kc[i] & 31;  // past the K range: any valid chunk, never used
+      lds_dma16(src[i] + k, smem + buf * SB + (wave * NI + i) * 1024);
+    }
+  };
+
+  f32x4_v acc[MBW][2];
+#pragma unroll
+  for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+  for (int st = 0; st < NS - 1; ++st)
+    if (st < nst) issue(st, st);
+  const int fo = r16 * SROWB + ((4 * ks + g) ^ r16) * 16;
+  int buf = 0;
+  for (int st = 0; st < nst; ++st) {
+    // stage st has landed once at most the stages issued after it are
+    // outstanding (in order); then the barrier: every wave's part of it is in
+    // LDS, and every wave is done with stage st - 1, whose buffer the next
+    // copies overwrite
+    const int after = min(nst - 1 - st, NS - 2);
+    if (after >= 6) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 * NI) : "memory");
+    else if (after == 5) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(5 * NI) : "memory");
+    else if (after == 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NI) : "memory");
+    else if (after == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NI) : "memory");
+    else if (after == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");
+    else if (after == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (st + NS - 1 < nst) issue(st + NS - 1, buf == 0 ? NS - 1 : buf - 1);
+    if (st * SKT + ks * 32 < klen) {
+      const unsigned char* sb = smem + buf * SB + fo;
+      uint4 bf[2], af[MBW];
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb) bf[nb] = *reinterpret_cast<const uint4*>(sb + (16 * MB + nb * 16) * SROWB);
+#pragma unroll
+      for (int mb = 0; mb < MBW; ++mb)
+        af[mb] = *reinterpret_cast<const uint4*>(sb + (mh * MBW + mb) * 16 * SROWB);
+#pragma unroll
+      for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) mfma_step(acc[mb][nb], af[mb], bf[nb], T());
+    }
+    buf = buf + 1 == NS ? 0 : buf + 1;
+  }
+
+  // sum of the four k-steps' partial tiles through the (now free) ring
+  wg_barrier_lds();
+  float* red = reinterpret_cast<float*>(smem);  // [4][16 MB][RCOLS]
+#pragma unroll
+  for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        red[(ks * 16 * MB + (mh * MBW + mb) * 16 + 4 * g + i) * RCOLS + nb * 16 + r16] = acc[mb][nb][i];
+  __syncthreads();
+  for (int e = threadIdx.x; e < 16 * MB * COLS; e += 512) {
+    const int row = e / COLS, col = e % COLS;
+    const int grow = m0 + row, gcol = n0 + col;
+    if (grow >= p.M || (PAIR == PAIR_NONE && gcol >= p.N)) continue;
+    float v = 0.f, u = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      v += red[(w * 16 * MB + row) * RCOLS + col];
+      if (PAIR) u += red[(w * 16 * MB + row) * RCOLS + col + 16];
+    }
+    epilogue_store<EPI, bf16_t>(p, z, split, grow, gcol, v, u);
+  }
+}
+
+// launch helper for the skinny kernel with the activations in LDS (bf16, M <= 16)
 template <int MB, int EPI>
 static void launch_skinny_lds_cfg(const GemmArgs& a, hipStream_t s, int nw) {
   constexpr int PAIR = EpiPair<EPI>::value;
@@ -1367,16 +1525,25 @@ __global__ __launch_bounds__(512) void gemm_big5(GemmArgs p) {
 // --------------------------------------------------------------------------
 static int skinny_mb(int M) { return M <= 16 ? 1 : (M <= 32 ? 2 : 4); }
 
-int gemm_pick_splits(int M, int N, int K, int elem_bytes) {
+// rows up to which a GEMM streams weight strips past all of its rows
+static int gemm_skinny_rows(int elem_bytes) { return elem_bytes == 2 ? 256 : 64; }
+static int stream_chunks(int M) { return (M + 127) / 128; }  // row ranges of at most 128
+// With more than 128 rows a split's K range is streamed only up to this length
+// (with 204 rows the output projection, 512 per split, 6.8 -> 6.2 us, but the
+// down projection, 1024 per split, 8.2 us against 7.4 on the tiles).
+constexpr int kStreamK = 512;
+
+int gemm_pick_splits(int M, int N, int K, int elem_bytes, bool stream) {
   const int ks = 64 / elem_bytes;
-  if (M <= 64) {
+  if (M <= 64 || (stream && M <= gemm_skinny_rows(elem_bytes))) {
     const int cols = 32;
-    const int base = (N + cols - 1) / cols;
+    const int base = (N + cols - 1) / cols * (M <= 64 ? 1 : stream_chunks(M));
     int maxs = K / (ks * 4 * 2);  // at least two k-steps per wave
     if (maxs < 1) maxs = 1;
-    int s = (256 + base - 1) / base;
+    int s = M <= 64 ? (256 + base - 1) / base : 256 / base;  // above 64 rows: within one wave of workgroups
     if (s > 8) s = 8;
-    return s < 1 ? 1 : (s > maxs ? maxs : s);
+    s = s < 1 ? 1 : (s > maxs ? maxs : s);
+    if (M <= 128 || (K + s - 1) / s <= kStreamK) return s;
   }
   const int base = ((N + TBN - 1) / TBN) * ((M + TBM - 1) / TBM);
   if (elem_bytes == 2) {
@@ -1435,6 +1602,34 @@ static void allow_large_lds(K kernel) {
 }
 
 template <int MB, int EPI>
+static void launch_stream_mb(const GemmArgs& a, int nx, hipStream_t s) {
+  constexpr int NS = stream_stages(MB, EPI), SB = stream_stage_bytes(MB);
+  allow_large_lds(gemm_stream<MB, EPI>);
+  const int klen = a.k_per_split < a.K ? a.k_per_split : a.K;
+  const int nst = (klen + SKT - 1) / SKT;
+  const int ring = (nst < NS ? nst : NS) * SB, red = 4 * 16 * MB * 33 * 4;
+  const dim3 grid(nx, (a.M + 16 * MB - 1) / (16 * MB) * a.splits, a.batch);
+  RFX_LAUNCH((gemm_stream<MB, EPI>), grid, dim3(512), ring > red ? ring : red, s, a);
+}
+
+template <int EPI>
+static void launch_stream(const GemmArgs& a, hipStream_t s) {
+  constexpr int PAIR = EpiPair<EPI>::value;
+  const int nx = PAIR == PAIR_HEAD ? a.N / 32 : (PAIR == PAIR_N ? a.N / 16 : (a.N + 31) / 32);
+  // rows per workgroup: the fewest that keep the grid within one workgroup per
+  // CU (less to copy for each); all of them, up to 128, when none does
+  int mb = a.M <= 32 ? 2 : (a.M <= 64 ? 4 : (a.M <= 96 ? 6 : 8));
+  for (int m = mb - 2; m >= 2; m -= 2)
+    if (nx * a.splits * a.batch * ((a.M + 16 * m - 1) / (16 * m)) <= 256) mb = m;
+  switch (mb) {
+    case 2: launch_stream_mb<2, EPI>(a, nx, s); break;
+    case 4: launch_stream_mb<4, EPI>(a, nx, s); break;
+    case 6: launch_stream_mb<6, EPI>(a, nx, s); break;
+    default: launch_stream_mb<8, EPI>(a, nx, s); break;
+  }
+}
+
+template <int MB, int EPI>
 static void launch_skinny_lds_pick(const GemmArgs& a, hipStream_t s) {
   constexpr int PAIR = EpiPair<EPI>::value;
   constexpr int NB = PAIR ? 1 : 2;
@@ -1449,26 +1644,20 @@ static void launch_skinny_lds_pick(const GemmArgs& a, hipStream_t s) {
 
 template <typename T, int EPI>
 static void launch_skinny(const GemmArgs& a, hipStream_t s) {
-  // bf16 with the activation K range fitting in LDS: stage it there
-  const int klen = a.k_per_split < a.K ? a.k_per_split : a.K;  // LDS holds one split's K range
-  if (sizeof(T) == 2 && (size_t)16 * skinny_mb(a.M) * ((klen * 2 + 127) & ~127) <= 160 * 1024 &&
-      a.k_per_split % 32 == 0 &&
-      a.K % 32 == 0) {
-    // an unsplit GEMM with few column strips (QKV at one env: 80) takes its
-    // rows in two 32-row halves: twice the workgroups, each copying half the
-    // activation rows; both halves of a strip land on the same XCD (nx is a
-    // multiple of 8), so its weights come from HBM once
-    constexpr int PAIR = EpiPair<EPI>::value;
-    const int nx = PAIR == PAIR_HEAD ? a.N / 32 : (PAIR == PAIR_N ? a.N / 16 : (a.N + 31) / 32);
-    if (skinny_mb(a.M) == 4 && a.splits == 1 && nx < 128 && nx % 8 == 0) {
-      launch_skinny_lds_pick<2, EPI>(a, s);
+  if constexpr (sizeof(T) == 2) {
+    if (a.M > 16 && a.k_per_split % 32 == 0 && a.K % 32 == 0) {
+      launch_stream<EPI>(a, s);
       return;
     }
-    switch (skinny_mb(a.M)) {
-      case 1: launch_skinny_lds_pick<1, EPI>(a, s); return;
-      case 2: launch_skinny_lds_pick<2, EPI>(a, s); return;
-      default: launch_skinny_lds_pick<4, EPI>(a, s); return;
-    }
+  }
+  // up to 16 rows with the activation K range fitting in LDS: stage it there
+  // (many more strips than CUs with 10 rows each, the conditioning MLPs of one
+  // env: several small workgroups per CU keep the weight stream up)
+  const int klen = a.k_per_split < a.K ? a.k_per_split : a.K;
+  if (sizeof(T) == 2 && a.M <= 16 && (size_t)16 * ((klen * 2 + 127) & ~127) <= 160 * 1024 &&
+      a.k_per_split % 32 == 0 && a.K % 32 == 0) {
+    launch_skinny_lds_pick<1, EPI>(a, s);
+    return;
   }
   switch (skinny_mb(a.M)) {
     case 1: launch_skinny_cfg<T, 1, EPI>(a, s); break;
@@ -1561,6 +1750,16 @@ static void launch_tiled(const GemmArgs& a, hipStream_t s) {
 template <typename T, int EPI>
 static void launch_pick(const GemmArgs& a, hipStream_t s) {
   bool skinny = a.M <= 64;
+  if constexpr (sizeof(T) == 2) {
+    // 65 .. 256 rows: weight strips while they fit one wave of workgroups
+    // (and always where the K split was planned for them)
+    constexpr int PAIR = EpiPair<EPI>::value;
+    const int nx = PAIR == PAIR_HEAD ? a.N / 32 : (PAIR == PAIR_N ? a.N / 16 : (a.N + 31) / 32);
+    if (a.M > 64 && a.M <= gemm_skinny_rows(2) && a.K % 32 == 0 && a.k_per_split % 32 == 0 &&
+        nx * stream_chunks(a.M) * a.splits * a.batch <= 256 &&
+        (a.M <= 128 || EPI != EPI_F32 || a.k_per_split <= kStreamK))
+      skinny = true;
+  }
   // paired tiles of the tiled kernel hold 64 first-half columns of one head
   if ((EPI == EPI_ROPE || EPI == EPI_KV) && a.qkv.head_dim < 128) skinny = true;
   if (skinny)

@@ -70,8 +70,9 @@ struct GemmArgs {
 };
 
 template <typename T> hipError_t launch_gemm(const GemmArgs& a, int epi, hipStream_t s);
-// Heuristic: number of K splits for an EPI_F32 GEMM.
-int gemm_pick_splits(int M, int N, int K, int elem_bytes);
+// Heuristic: number of K splits for an EPI_F32 GEMM.  stream: for the form the
+// launcher takes; without it as if 65 and more rows always ran on the tiles.
+int gemm_pick_splits(int M, int N, int K, int elem_bytes, bool stream = true);
 
 // Partitioned-region attention (Eq. 1) for the dynamic rows of every env.
 struct AttnArgs {
@@ -109,6 +110,7 @@ enum AttnKernel : int { ATTN_AUTO = 0, ATTN_ROWS16 = 1, ATTN_PAIR = 2, ATTN_ROWS
 struct AttnPlan {
   int kernel;
   int splits;
+  int few_splits;  // the count without the team kernel (at most 16)
 };
 AttnPlan attention_plan(int B, int rows, int head_dim, int max_keys, int elem_bytes, int force);
 

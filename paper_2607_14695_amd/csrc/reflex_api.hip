@@ -99,7 +99,7 @@ size_t static_scratch_bytes(const Plan& P) { return P.off[17] - P.off[1]; }
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 SplitK make_split(int M, int K, int splits, int eb) {
-  // skinny kernels step K in 64-byte k-steps, tiled kernels in 128-byte stages
+  // up to 64 rows: 64-byte k-steps; more: the tiled kernels' 128-byte stages
   const int gran = (M <= 64 ? 64 : 128) / eb;
   SplitK s;
   if (splits < 1) splits = 1;
@@ -156,13 +156,12 @@ Plan make_plan(const reflex_config* c) {
   const int rows = p.T * c->n_q_heads;
   p.rows_pad = (rows + 127) / 128 * 128;
   p.tpad = (p.T + 63) / 64 * 64;
-  p.o = make_split(p.M, c->n_q_heads * c->head_dim,
-                   gemm_pick_splits(p.M, c->width, c->n_q_heads * c->head_dim, eb), eb);
+  const int Ko = c->n_q_heads * c->head_dim;
+  p.o = make_split(p.M, Ko, gemm_pick_splits(p.M, c->width, Ko, eb), eb);
   p.down = make_split(p.M, c->mlp_dim, gemm_pick_splits(p.M, c->width, c->mlp_dim, eb), eb);
   const AttnPlan ap = attention_plan(c->batch, rows, c->head_dim, p.R, eb, c->attn_kernel);
   p.attn_splits = ap.splits;
   p.attn_kernel = ap.kernel;
-  p.max_parts = p.o.splits > p.down.splits ? p.o.splits : p.down.splits;
 
   const size_t B = c->batch, L = c->n_layers, dh = c->head_dim, D = c->width, K = c->max_steps;
   p.cache_bytes = align256(B * L * p.R * dh * eb) * 2;
@@ -181,10 +180,7 @@ Plan make_plan(const reflex_config* c) {
   sz[10] = B * dh * (size_t)p.tpad * eb;                                  // vdt
   sz[11] = 0;  // (unused)
   sz[12] = (size_t)p.M * c->n_q_heads * dh * eb;                          // o
-  sz[13] = B * p.attn_splits * (size_t)p.rows_pad * dh * eb;              // part_o (element type: bf16 or fp32)
-  sz[14] = B * p.attn_splits * (size_t)p.rows_pad * 2 * sizeof(float);    // part_ml
   sz[15] = (size_t)p.M * c->mlp_dim * eb;                                 // z
-  sz[16] = (size_t)p.max_parts * p.M * D * sizeof(float);                 // rparts
   sz[17] = 0;  // (unused: the frame projection writes the cache from its epilogue)
   p.naive_k_stride = align256(sz[9]);
   p.naive_vt_stride = align256(sz[10]);
@@ -192,23 +188,35 @@ Plan make_plan(const reflex_config* c) {
   sz[19] = L * p.naive_vt_stride;                                         // naive_vt
   sz[20] = (size_t)p.M * (p.Nqkv > 2 * c->mlp_dim ? p.Nqkv : 2 * c->mlp_dim) * sizeof(float);  // uf_wide
   sz[21] = (size_t)p.M * c->action_dim * sizeof(float);                   // uf_v
-  auto lay_out = [&] {
+  // attention partials (bf16 or fp32) and residual partials: room for the
+  // plan's split counts, and at least for the few ones (up to 16 key splits,
+  // sized as fp32; the tiles' K splits).  Whether a chunk fits the static array
+  // of the allocation-free entry point is decided by the few alone: where they
+  // fit and the plan's counts would not, the few are taken.
+  const size_t part = B * (size_t)p.rows_pad * dh, few_o = ap.few_splits * part * sizeof(float);
+  const SplitK of = make_split(p.M, Ko, gemm_pick_splits(p.M, c->width, Ko, eb, false), eb);
+  const SplitK df = make_split(p.M, c->mlp_dim, gemm_pick_splits(p.M, c->width, c->mlp_dim, eb, false), eb);
+  const int few_parts = of.splits > df.splits ? of.splits : df.splits;
+  auto lay_out = [&](int key_splits, int parts) {
+    const size_t ks = key_splits > ap.few_splits ? key_splits : ap.few_splits;
+    p.max_parts = parts > few_parts ? parts : few_parts;
+    sz[13] = key_splits * part * eb > few_o ? key_splits * part * eb : few_o;  // part_o
+    sz[14] = B * ks * p.rows_pad * 2 * sizeof(float);                         // part_ml
+    sz[16] = (size_t)p.max_parts * p.M * D * sizeof(float);                   // rparts
     size_t off = 0;
     for (int i = 0; i < kWsParts; ++i) {
       p.off[i] = off;
       off += align256(sz[i]);
     }
     p.ws_bytes = off;
+    return static_scratch_bytes(p) <= kScratchBytes;
   };
-  lay_out();
-  // more than 16 key splits only while the chunk still fits the static scratch
-  // array of the allocation-free entry point (16 splits always took more bytes
-  // there when partials were sized as fp32)
-  if (p.attn_splits > 16 && static_scratch_bytes(p) > kScratchBytes) {
-    p.attn_splits = 16;
-    sz[13] = B * p.attn_splits * (size_t)p.rows_pad * dh * eb;
-    sz[14] = B * p.attn_splits * (size_t)p.rows_pad * 2 * sizeof(float);
-    lay_out();
+  const bool few_fit = lay_out(ap.few_splits, few_parts);
+  if (!lay_out(p.attn_splits, p.o.splits > p.down.splits ? p.o.splits : p.down.splits) && few_fit) {
+    p.attn_splits = ap.few_splits;
+    p.o = of;
+    p.down = df;
+    lay_out(p.attn_splits, few_parts);
   }
   return p;
 }
