@@ -801,9 +801,9 @@ constexpr int DSTAGE = (TBM + TBN) * DROWB;  // bytes per stage (32 KB)
 
 // Workgroup -> tile.  Workgroups are dispatched round-robin over the 8 XCDs,
 // each with its own L2.  With a 1-D grid, XCD x receives the tiles
-// [x*per, (x+1)*per) of the tile sequence in which the M tile varies fastest,
-// so the workgroups sharing an L2 also share B (weight) tiles and a band of
-// A tiles instead of touching every tile of both operands.
+// [x*per, (x+1)*per) of the tile sequence, M fastest, so the workgroups sharing
+// an L2 also share B (weight) tiles and a band of A tiles instead of touching
+// every tile of both operands.
 template <int PAIR, int BM>
 RFX_DEV bool dma_tile(const GemmArgs& p, int& bx, int& by, int& bz) {
   const int nx = PAIR == PAIR_NONE ? (p.N + TBN - 1) / TBN : p.N / (PAIR == PAIR_N ? 64 : 128);
@@ -816,6 +816,31 @@ RFX_DEV bool dma_tile(const GemmArgs& p, int& bx, int& by, int& bz) {
   const int rest = t / ny;
   bx = rest % nx;
   bz = rest / nx;
+  return true;
+}
+
+// The same through groups of p.tile_group M tiles by every N tile, M fastest
+// within a group, so that the tiles of one XCD form about a square.  The
+// two-group kernel takes it (26 x 8 tiles of the down projection at 32 envs
+// and 101 tokens, K = 4096: an XCD's tiles span 11 MB of A and B instead of
+// 27; 42.4 -> 35.9 us); on the unrolled pipeline it was not faster (long
+// context, chunk 16.80 -> 16.97 ms).
+template <int PAIR, int BM>
+RFX_DEV bool group_tile(const GemmArgs& p, int& bx, int& by, int& bz) {
+  const int nx = PAIR == PAIR_NONE ? (p.N + TBN - 1) / TBN : p.N / (PAIR == PAIR_N ? 64 : 128);
+  const int ny = (p.M + BM - 1) / BM;
+  const int total = nx * ny * p.batch * p.splits;
+  const int per = (total + 7) / 8;
+  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (t >= total) return false;
+  const int tz = nx * ny, gmax = p.tile_group;
+  bz = t / tz;
+  const int tt = t - bz * tz;
+  const int grp = tt / (gmax * nx);
+  const int gm = min(gmax, ny - grp * gmax);
+  const int r = tt - grp * gmax * nx;
+  bx = r / gm;
+  by = grp * gmax + r - bx * gm;
   return true;
 }
 
@@ -1169,6 +1194,237 @@ __global__ __launch_bounds__(256 * KW) void gemm_dma(GemmArgs p) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             if (gcol + e < p.N) epilogue_store<EPI, T>(p, z, split, grow, gcol + e, v[e], 0.f);
+        }
+      }
+    }
+  }
+}
+
+// --------------------------------------------------------------------------
+// tiled, bf16, BM x 128 tiles, any number of stages: the one-wave grids whose K
+// range is none of the unrolled pipeline's (8, 16 or 32 stages), which ran on
+// the two-stage kernel (down projection of 3,232 rows, 64 stages: 71.9 -> 37.2
+// us).  Two wave groups run half a stage apart.  Four output blocks (2 x 2 of
+// BM/2 x 64) have two waves each, one per 32-wide k-step of a 64-element stage;
+// the waves of k-step 0 are group 0, those of k-step 1 group 1, and every SIMD
+// holds one wave of each.  While one group issues the MFMAs of a stage, the
+// other reads its fragments of it from LDS:
+//   interval 2s:    group 0 reads (s)    group 1 MFMAs (s-1)
+//   interval 2s+1:  group 0 MFMAs (s)    group 1 reads (s)
+// with a barrier after each.  Reads are complete before the barrier that ends
+// their interval, so the buffer of stage s is free from interval 2s+2 on, where
+// the copies of stage s + NS start, half of a wave's share per half stage.
+// Stage s + 1 has landed (each wave's share, then the barrier) when interval
+// 2s+1 ends.  Without copies a stage of 128 rows takes 580 cycles (its MFMAs
+// 512), with them 980: they, and the fabric behind the L2, bound it; at 8, 16
+// and 32 stages the unrolled kernel is as fast or faster.
+//
+// At the end the two waves of a block exchange halves of their partial sums
+// through LDS and each finalizes the other half (a + b = b + a).
+// --------------------------------------------------------------------------
+constexpr int pp_stage_bytes(int BM) { return (BM + TBN) * DROWB; }
+constexpr int pp_stages(int BM) { return BM == 128 ? 4 : 6; }
+
+template <int EPI, int BM>
+__global__ __launch_bounds__(512) void gemm_pp(GemmArgs p) {
+  using T = bf16_t;
+  constexpr int PAIR = EpiPair<EPI>::value;
+  constexpr int NS = pp_stages(BM), STB = pp_stage_bytes(BM);
+  constexpr int MB = BM / 32;           // A copies per output block and stage
+  constexpr int MB2 = BM / 64;          // 32-row blocks of a wave
+  constexpr int CPS = MB + 4;           // copies per output block and stage
+  constexpr int CPW = (CPS + 1) / 2;    // copies per wave and stage (an odd count repeats the last)
+  static_assert(BM == 128 || BM == 64, "128- or 64-row tiles");
+  __shared__ __attribute__((aligned(16))) unsigned char smem[NS * STB];
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r32 = lane & 31, h32 = lane >> 5;
+  const int wq = wave & 3, wk = wave >> 2;  // output block, k-step (= group)
+  const int wm = wq >> 1, wn = wq & 1;
+  int bx, by, bz;
+  if (!group_tile<PAIR, BM>(p, bx, by, bz)) return;
+  const int z = bz / p.splits, split = bz % p.splits;
+  const int m0 = by * BM;
+  int n0, pair_off;
+  if constexpr (PAIR == PAIR_HEAD) {
+    const int half = p.qkv.head_dim >> 1, per_head = half / 64;
+    const int h = bx / per_head;
+    n0 = h * p.qkv.head_dim + (bx - h * per_head) * 64;
+    pair_off = half;
+  } else if constexpr (PAIR == PAIR_N) {
+    n0 = bx * 64;
+    pair_off = p.N;
+  } else {
+    n0 = bx * TBN;
+    pair_off = 0;
+  }
+  const int kbeg = split * p.k_per_split;
+  const int nst = (min(p.K, kbeg + p.k_per_split) - kbeg) / DST;
+
+  const T* A = reinterpret_cast<const T*>(p.A) + (int64_t)z * p.a_bstride;
+  const T* B = reinterpret_cast<const T*>(p.B) + (int64_t)z * p.b_bstride;
+  // copy i of this wave (as in gemm_dma: eight whole 128-byte rows per
+  // instruction, chunk lane & 7 holding logical chunk (lane & 7) ^ swizzle)
+  const T* gsrc[CPW];
+  int lrow[CPW];
+  {
+    const int rr = lane >> 3, pc = lane & 7;
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+      const int j = min(wk * CPW + i, CPS - 1);
+      const bool isa = j < MB;
+      const int row0 = isa ? 8 * (MB * wq + j) : 8 * (4 * wq + j - MB);
+      const int row = row0 + rr;
+      lrow[i] = isa ? row0 : BM + row0;
+      const int lc = pc ^ RFX_GSWZ(row);
+      if (isa) {
+        gsrc[i] = A + (int64_t)min(m0 + row, p.M - 1) * p.lda + kbeg + lc * 8;
+      } else {
+        int brw;
+        if (PAIR != PAIR_NONE) brw = n0 + (row & 63) + (row >= 64 ? pair_off : 0);
+        else brw = min(n0 + row, p.N - 1);
+        gsrc[i] = B + (int64_t)brw * p.ldb + kbeg + lc * 8;
+      }
+    }
+  }
+  // copies i0 .. i1 - 1 of a stage.  A CU takes 16 to 18 cycles per copy and a
+  // wave that runs ahead of that stands still, so each half stage issues half
+  constexpr int CH = CPW / 2;
+  auto issue = [&](int st, int buf, int i0, int i1) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = i0; i < i1; ++i) lds_dma16(gsrc[i] + st * DST, smem + buf * STB + lrow[i] * DROWB);
+  };
+  // this wave's share of a stage has landed once at most the `after` stages
+  // issued later are outstanding
+  auto landed = [&](int after) __attribute__((always_inline)) {
+    if (after >= 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * CPW) : "memory");
+    else if (after == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * CPW) : "memory");
+    else if (after == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CPW) : "memory");
+    else if (after == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CPW) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+  auto bar = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  f32x16_v acc[MB2][2];  // C^T blocks [32-row block][32-column block] (nb 1: the paired columns of 0)
+#pragma unroll
+  for (int a = 0; a < MB2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = f32x16_v{};
+  // fragment offsets within a stage: half k-steps 2 wk and 2 wk + 1, chunk
+  // 2 kk + h32 of row r32
+  uint32_t fo[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) fo[kk] = r32 * DROWB + ((2 * (2 * wk + kk) + h32) ^ RFX_GSWZ(r32)) * 16;
+  uint4 af[2 * MB2], bf[4];
+  auto read = [&](int buf) __attribute__((always_inline)) {
+    const unsigned char* sb = smem + buf * STB;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+        bf[kk * 2 + nb] = *reinterpret_cast<const uint4*>(
+            sb + (BM + (PAIR != PAIR_NONE ? nb * 64 + wn * 32 : wn * 64 + nb * 32)) * DROWB + fo[kk]);
+#pragma unroll
+      for (int mb = 0; mb < MB2; ++mb)
+        af[kk * MB2 + mb] = *reinterpret_cast<const uint4*>(sb + (wm * (BM / 2) + mb * 32) * DROWB + fo[kk]);
+    }
+  };
+  // the stage's MFMAs; after the first half of them copies i0 .. i1 - 1 of stage
+  // st (if there is one)
+  auto math = [&](int st, int sbuf, int i0, int i1) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int mb = 0; mb < MB2; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) mfma32_step(acc[mb][nb], bf[kk * 2 + nb], af[kk * MB2 + mb]);
+      if (kk == 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (st < nst) issue(st, sbuf, i0, i1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
+  };
+
+#pragma unroll
+  for (int st = 0; st < NS; ++st)
+    if (st < nst) issue(st, st, 0, CPW);
+  landed(min(nst, NS) - 1);
+  bar();
+  int buf = 0;  // of stage s
+  if (wk == 0) {
+    for (int s = 0; s < nst; ++s) {
+      const int ni = s > 0 ? s - 1 + NS : nst, nbuf = buf == 0 ? NS - 1 : buf - 1;  // stage copied next
+      read(buf);
+      if (ni < nst) issue(ni, nbuf, 0, CH);
+      bar();
+      math(ni, nbuf, CH, CPW);
+      if (s + 1 < nst) landed(min(nst - 1, s - 1 + NS) - (s + 1));
+      bar();
+      buf = buf + 1 == NS ? 0 : buf + 1;
+    }
+    bar();
+  } else {
+    bar();
+    for (int s = 0; s < nst; ++s) {
+      const int ni = s > 0 ? s - 1 + NS : nst, nbuf = buf == 0 ? NS - 1 : buf - 1;
+      read(buf);
+      if (ni < nst) issue(ni, nbuf, CH, CPW);
+      if (s + 1 < nst) landed(min(nst - 1, s - 1 + NS) - (s + 1));
+      bar();
+      math(s + NS, buf, 0, CH);
+      bar();
+      buf = buf + 1 == NS ? 0 : buf + 1;
+    }
+  }
+
+  // the hand-over: every copy has landed and every fragment read is done, so
+  // the ring is free
+  // a lane holds four groups of four consecutive columns per block: wave wk
+  // finalizes groups 2 wk and 2 wk + 1 and hands over the others
+  constexpr int NX = MB2 * 2 * 2;  // float4s handed over per lane
+  static_assert(8 * NX * 64 * 16 <= NS * STB, "hand-over fits the ring");
+  float4* const sendp = reinterpret_cast<float4*>(smem) + wave * (NX * 64) + lane;
+  const float4* const recvp = reinterpret_cast<const float4*>(smem) + (wave ^ 4) * (NX * 64) + lane;
+#pragma unroll
+  for (int mb = 0; mb < MB2; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const f32x16_v& a = acc[mb][nb];
+        sendp[((mb * 2 + nb) * 2 + j) * 64] =
+            wk ? make_float4(a[4 * j], a[4 * j + 1], a[4 * j + 2], a[4 * j + 3])
+               : make_float4(a[8 + 4 * j], a[8 + 4 * j + 1], a[8 + 4 * j + 2], a[8 + 4 * j + 3]);
+      }
+  bar();
+#pragma unroll
+  for (int mb = 0; mb < MB2; ++mb) {
+    const int grow = m0 + wm * (BM / 2) + mb * 32 + r32;
+    float v[2][2][4];  // [nb][j]
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float4 r = recvp[((mb * 2 + nb) * 2 + j) * 64];
+        const f32x16_v& a = acc[mb][nb];
+        const float o[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[nb][j][e] = (wk ? a[8 + 4 * j + e] : a[4 * j + e]) + o[e];
+      }
+    if (grow >= p.M) continue;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int c = 8 * (2 * wk + j) + 4 * h32;
+      if (PAIR != PAIR_NONE) {
+        epilogue_store4<EPI>(p, z, split, grow, n0 + wn * 32 + c, v[0][j], v[1][j]);
+      } else {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+          const int gcol = n0 + wn * 64 + nb * 32 + c;
+          if (gcol < p.N) epilogue_store4<EPI>(p, z, split, grow, gcol, v[nb][j], v[nb][j]);  // N is a multiple of 4
         }
       }
     }
@@ -1692,6 +1948,15 @@ static void launch_tiled(const GemmArgs& a, hipStream_t s) {
         RFX_LAUNCH((gemm_big<EPI>), g, dim3(512), 0, s, a);
       return;
     }
+    const int cols = nx * a.batch * a.splits;
+    auto tiles = [&](int bm) { return cols * ((a.M + bm - 1) / bm); };
+    GemmArgs t = a;
+    auto group = [&](int bm) {  // M tiles of a group: an XCD's tiles about square in rows and columns
+      const int ny = (a.M + bm - 1) / bm;
+      int gm = 1;
+      while ((gm + 1) * gm * bm <= (tiles(bm) + 7) / 8 * TBN) ++gm;
+      t.tile_group = gm < ny ? gm : ny;
+    };
     // four-stage unrolled pipeline (one workgroup per CU) when one wave of
     // workgroups covers the grid; else the two-stage one (two per CU).  The
     // stage count is that of every split's K range (a single split may be
@@ -1739,8 +2004,12 @@ static void launch_tiled(const GemmArgs& a, hipStream_t s) {
         if (t64) RFX_LAUNCH((gemm_dma<EPI, 4, 32, 64, false, KE>), g64, dim3(256 * KE), 0, s, a);
         else RFX_LAUNCH((gemm_dma<EPI, 4, 32>), g128, dim3(256), 0, s, a);
       }
+    } else if (tiles(64) <= 256) {
+      group(64);
+      RFX_LAUNCH((gemm_pp<EPI, 64>), dim3((tiles(64) + 7) / 8 * 8), dim3(512), 0, s, t);
     } else {
-      RFX_LAUNCH((gemm_dma<EPI, 2, 0>), dim3((total + 7) / 8 * 8), dim3(256), 0, s, a);
+      group(128);
+      RFX_LAUNCH((gemm_pp<EPI, 128>), dim3((total + 7) / 8 * 8), dim3(512), 0, s, t);
     }
   }
   else

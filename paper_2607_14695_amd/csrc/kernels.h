@@ -65,6 +65,7 @@ struct GemmArgs {
   int k_per_split;   // multiple of the k-step
   int mod_width;     // EPI_MOD: width D, 0 = full modulation
   int batch;         // blockIdx.z extent
+  int tile_group;    // gemm_pp: M tiles per group of the tile order (set by launch_gemm)
   QkvOut qkv;        // EPI_ROPE; EPI_KV uses qkv.head_dim only
   KvOut kv;          // EPI_KV only
 };

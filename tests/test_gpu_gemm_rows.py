@@ -53,3 +53,15 @@ def test_streamed_row_chunks(batch, tokens):
     of the longest one that is streamed; rows of several envs in one range."""
     _check(BASE.replace(batch=batch, action_horizon=tokens - 1, width=320, mlp_dim=640, n_q_heads=3, head_dim=128))
     _check(BASE.replace(batch=batch, action_horizon=tokens - 1, width=128, mlp_dim=4160, n_q_heads=2, head_dim=64))
+
+
+@pytest.mark.parametrize("changes", [
+    # 300 rows, 64-row tiles: 5, 6 and 27 stages of 64, a last row tile of 44 rows, 320 columns
+    dict(batch=5, action_horizon=59, width=320, mlp_dim=1728, n_q_heads=3, head_dim=128, frame_dim=320),
+    # 2,100 rows, 128-row tiles for the gate|up projection: 15 stages; 64-row ones for the others
+    dict(batch=25, action_horizon=83, width=960, mlp_dim=896, n_q_heads=2, head_dim=128, n_layers=1, num_steps=1),
+])
+def test_odd_stage_counts(changes):
+    """More than 256 rows with K ranges of no power-of-two stage count: every epilogue of the two-group tiles
+    (fp32, RoPE, gated GELU, and the frame K/V projection of 320 rows with 5 stages)."""
+    _check(BASE.replace(frame_tokens=64, **changes))
