@@ -265,13 +265,15 @@ _EPI_CLASS = {"4": "gemm_qkv", "2": "gemm_gate_up", "5": "frame_proj", "1": "mod
 
 def _epi(name: str) -> Optional[str]:
     """Epilogue template argument of a GEMM kernel name (its first argument,
-    or the third for the skinny kernels)."""
+    the second for the streaming kernel, the third for the skinny kernels)."""
     m = re.search(r"gemm_(\w+)<([^>]*)>", name)
     if not m:
         return None
     args = [a.strip() for a in m.group(2).split(",")]
     if m.group(1) in ("skinny_lds",):
         return args[2] if len(args) > 2 else None
+    if m.group(1) == "stream":
+        return args[1] if len(args) > 1 else None
     if m.group(1) in ("skinny", "tiled"):
         return args[3] if m.group(1) == "skinny" and len(args) > 3 else (args[1] if len(args) > 1 else None)
     return args[0]
@@ -285,7 +287,7 @@ def classify(names: List[str]) -> List[str]:
     for n in names:
         if "reflex::" not in n:
             c = "other"
-        elif re.search(r"attn(16p|16|_pair)?_kernel", n):
+        elif re.search(r"attn(16p|16|_pair|_team)?_kernel", n):
             c = "attention"
         elif "attn_merge" in n:
             c = "attn_merge"

@@ -136,3 +136,12 @@ def test_stamp_validation_takes_only_the_stamped_dispatches(tmp_path):
     assert r["stamped"] == 3
     assert abs(r["trace_us"] - (8.0 + 10.0 + 8.0) / 3) < 1e-9
     assert abs(r["ratio"] - 8.5 / r["trace_us"]) < 1e-12
+
+
+def test_classify_names_streaming_and_team_kernels():
+    seq = ["reflex::gemm_stream<4, 4>(x)", "reflex::attn_team_kernel<256>(x)",
+           "reflex::attn_merge_wide_kernel<256>(x)", "reflex::gemm_stream<4, 0>(x)",
+           "reflex::resid_norm_kernel<unsigned short, 1>(x)", "reflex::gemm_stream<4, 2>(x)",
+           "reflex::gemm_pp<0, 128>(x)"]
+    assert P.classify(seq) == ["gemm_qkv", "attention", "attn_merge", "gemm_o", "resid_norm", "gemm_gate_up",
+                               "gemm_down"]
