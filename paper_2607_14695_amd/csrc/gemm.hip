@@ -1850,17 +1850,17 @@ static void launch_skinny_cfg(const GemmArgs& a, hipStream_t s) {
 }
 
 // dynamic LDS above the default 64 KB limit must be allowed per kernel, once
-template <typename K>
-static void allow_large_lds(K kernel) {
+template <void (*K)(GemmArgs)>
+static void allow_large_lds() {
   static const hipError_t once =
-      hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   (void)once;
 }
 
 template <int MB, int EPI>
 static void launch_stream_mb(const GemmArgs& a, int nx, hipStream_t s) {
   constexpr int NS = stream_stages(MB, EPI), SB = stream_stage_bytes(MB);
-  allow_large_lds(gemm_stream<MB, EPI>);
+  allow_large_lds<gemm_stream<MB, EPI>>();
   const int klen = a.k_per_split < a.K ? a.k_per_split : a.K;
   const int nst = (klen + SKT - 1) / SKT;
   const int ring = (nst < NS ? nst : NS) * SB, red = 4 * 16 * MB * 33 * 4;
@@ -1892,9 +1892,9 @@ static void launch_skinny_lds_pick(const GemmArgs& a, hipStream_t s) {
   // eight waves when every wave gets at least two k-steps
   const int nw = a.k_per_split >= 16 * 32 ? 8 : 4;
   if (nw == 8)
-    allow_large_lds(gemm_skinny_lds<MB, NB, EPI, 8>);
+    allow_large_lds<gemm_skinny_lds<MB, NB, EPI, 8>>();
   else
-    allow_large_lds(gemm_skinny_lds<MB, NB, EPI, 4>);
+    allow_large_lds<gemm_skinny_lds<MB, NB, EPI, 4>>();
   launch_skinny_lds_cfg<MB, EPI>(a, s, nw);
 }
 
