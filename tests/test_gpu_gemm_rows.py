@@ -17,10 +17,10 @@ BASE = WL.CONFIGS["tiny_fp32"].replace(
     frame_tokens=24, window_frames=2, frame_dim=0, mod_mode="scale_only", batch=1)
 
 
-def _check(cfg):
+def _check(cfg, head=4):
     w = WL.make_weights(cfg)
-    for name in ("w_o", "w_down", "w_aout"):
-        w[name] *= np.float32(4)  # exact in bf16; the actions depend on every projection
+    for name, scale in (("w_o", 4), ("w_down", 4), ("w_aout", head)):
+        w[name] *= np.float32(scale)  # exact in bf16; the actions depend on every projection
     sk, sv = WL.make_static_kv(cfg)
     frames = {t: WL.make_frame(cfg, t) for t in range(2)}
     eng = R.ReflexEngine(cfg, w, sk, sv)
@@ -65,3 +65,35 @@ def test_odd_stage_counts(changes):
     """More than 256 rows with K ranges of no power-of-two stage count: every epilogue of the two-group tiles
     (fp32, RoPE, gated GELU, and the frame K/V projection of 320 rows with 5 stages)."""
     _check(BASE.replace(frame_tokens=64, **changes))
+
+
+@pytest.mark.parametrize("rows", [17, 32, 33, 64])
+def test_streamed_strips_beyond_one_wave(rows):
+    """More streaming workgroups than CUs (small rings, two workgroups per CU): gate|up of 4,160 columns (260
+    strips), the output and down projections as 40 strips by seven K ranges of 448 and 608 (3.5 and 4.75
+    stages, more than the ring's), and QKV with 64 heads of 128 (264 strips).  The action head is scaled by 2 at 1,280
+    columns: a velocity is about scale * 0.02 * sqrt(width), 1.4 here as in the cases of 320, and the absolute
+    bar is meant for actions of order one (with 4, actions of 5.6 differed by 5.6e-2 at rel-L2 5.8e-3)."""
+    _check(BASE.replace(action_horizon=rows - 1, width=1280, mlp_dim=4160, n_q_heads=12, head_dim=256, n_layers=1),
+           head=2)
+    _check(BASE.replace(action_horizon=rows - 1, width=704, mlp_dim=128, n_q_heads=64, head_dim=128, n_layers=1))
+
+
+@pytest.mark.parametrize("batch,tokens", [(1, 24), (1, 40), (2, 32)])
+def test_streamed_frame_projection_beyond_one_wave(batch, tokens):
+    """The K/V projection of 17 layers of 256-wide heads as 272 strips over 24, 40 and 64 frame rows: the cache
+    rows against the oracle's (results rounded to bf16, 2^-9 each; sums in fp32)."""
+    cfg = BASE.replace(batch=batch, n_layers=17, width=64, mlp_dim=64, n_q_heads=1, head_dim=256, frame_tokens=tokens,
+                       frame_dim=736)
+    w = WL.make_weights(cfg)
+    frame = WL.make_frame(cfg, 0)
+    eng = R.ReflexEngine(cfg, w, *WL.make_static_kv(cfg))
+    eng.write_frame(frame)
+    K, Vt = [x.float().cpu().numpy() for x in eng.cache_views()]
+    rows = slice(cfg.static_len, cfg.static_len + tokens)
+    for env in range(batch):
+        for l in range(cfg.n_layers):
+            kf, vf = O.frame_kv(cfg, w, frame[env], 0, l)
+            for got, ref in ((K[env, l, rows], kf[:, 0]), (Vt[env, l, :, rows], vf[:, 0].T)):
+                assert np.linalg.norm(got - ref) <= 4e-3 * np.linalg.norm(ref), (env, l)
+    eng.close()
