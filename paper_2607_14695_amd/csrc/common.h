@@ -114,9 +114,13 @@ RFX_DEV void lds_dma16(const void* g, void* lds) {
                :: "v"(g), "s"((unsigned)(size_t)lds) : "memory");
 }
 
-// The same from a wave-uniform base and a 32-bit byte offset per lane.
+// The same from a wave-uniform base and a 32-bit byte offset per lane.  The
+// base may come straight out of a vector instruction (v_readfirstlane, a
+// restored spill): five wait states must pass between such a write and the
+// copy that reads the scalar pair, and the compiler's hazard pass does not look
+// into inline assembly, so they are taken here (one for s_mov, four for s_nop 3).
 RFX_DEV void lds_dma16(const void* base, uint32_t off, void* lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
                :: "v"(off), "s"(base), "s"((unsigned)(size_t)lds) : "memory");
 }
 
