@@ -471,25 +471,25 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_lds(GemmArgs p) {
 constexpr int SKT = 128;          // K elements per stage
 constexpr int SROWB = SKT * 2;    // bytes per stage row
 constexpr int stream_stage_bytes(int MB) { return (16 * MB + 32) * SROWB; }
-// Stages of the ring.  A grid of more than one workgroup per CU takes a ring
-// small enough for two per CU, so that the next workgroups start under the
-// first ones (18 layers, weights from HBM; one per CU against two: gate|up with
-// 25 rows and 260 / 384 strips 9.8 -> 7.5 / 9.9 -> 7.6 us, with 51 rows and 384
-// strips 12.1 -> 9.9; output projection of width 1280 in 320 workgroups 7.6 ->
-// 6.1).  Within one wave the deep ring keeps more of the weights in flight (101
-// rows, width 2048: QKV 10.0 us, small ring 10.5).  The conditioning MLPs take
-// the small ring at any grid (20 rows, 48 and 144 strips: 10.6 us for both and
-// their input, deep ring 11.0; thousands of strips 26.4 against 31.1).  With 96
-// and 128 rows no two workgroups fit.
-constexpr int stream_stages(int MB, bool shallow) {
-  return MB <= 2 ? (shallow ? 4 : 8) : (MB <= 4 ? (shallow ? 3 : 6) : 4);
-}
+// Stages of the ring.  Rings small enough for two workgroups per CU, where the
+// rows allow it: in a grid of more than one per CU the next workgroups start
+// under the first ones (18 layers, weights from HBM, one ring per CU against
+// two: gate|up with 25 rows and 260 / 384 strips 9.8 -> 7.5 / 9.9 -> 7.6 us, with
+// 51 rows and 384 strips 12.1 -> 9.9; output projection of width 1280 in 320
+// workgroups 7.6 -> 6.1).  Within one wave, 64-row workgroups keep a deep ring,
+// which has more of the weights in flight (101 rows, width 2048: QKV 10.0 us,
+// small ring 10.5; 51 rows, width 4096: gate|up 18.1 and 19.5), except for the
+// conditioning MLPs (60 rows, both and their input: 13.3 us, deep ring 13.9).
+// With 32 rows a deep ring of eight stages was nowhere faster (17 to 32 rows,
+// QKV of width 512 / 1024 / 2048 / 4096: 4.4 -> 4.3, 5.7 -> 5.3, 8.1 -> 7.6, 11.6
+// -> 11.5 us).  With 96 and 128 rows no two workgroups fit.
+constexpr int stream_stages(int MB, bool deep) { return MB == 4 ? (deep ? 6 : 3) : 4; }
 
-template <int MB, int EPI, bool SHALLOW>
+template <int MB, int EPI, bool DEEP>
 __global__ __launch_bounds__(512) void gemm_stream(GemmArgs p) {
   using T = bf16_t;
   constexpr int PAIR = EpiPair<EPI>::value;
-  constexpr int NS = stream_stages(MB, SHALLOW), SB = stream_stage_bytes(MB);
+  constexpr int NS = stream_stages(MB, DEEP), SB = stream_stage_bytes(MB);
   constexpr int COLS = PAIR ? 16 : 32;  // first columns per workgroup
   constexpr int MBW = MB / 2;           // 16-row blocks per wave
   constexpr int NI = MB / 2 + 1;        // copy instructions per wave and stage
@@ -1864,26 +1864,23 @@ static void allow_large_lds() {
   (void)once;
 }
 
-template <int MB, int EPI, bool SHALLOW>
+template <int MB, int EPI, bool DEEP = false>
 static void launch_stream_ring(const GemmArgs& a, dim3 grid, hipStream_t s) {
-  constexpr int NS = stream_stages(MB, SHALLOW), SB = stream_stage_bytes(MB);
-  allow_large_lds<gemm_stream<MB, EPI, SHALLOW>>();
+  constexpr int NS = stream_stages(MB, DEEP), SB = stream_stage_bytes(MB);
+  allow_large_lds<gemm_stream<MB, EPI, DEEP>>();
   const int klen = a.k_per_split < a.K ? a.k_per_split : a.K;
   const int nst = (klen + SKT - 1) / SKT;
   const int ring = (nst < NS ? nst : NS) * SB, red = 4 * 16 * MB * 33 * 4;
-  RFX_LAUNCH((gemm_stream<MB, EPI, SHALLOW>), grid, dim3(512), ring > red ? ring : red, s, a);
+  RFX_LAUNCH((gemm_stream<MB, EPI, DEEP>), grid, dim3(512), ring > red ? ring : red, s, a);
 }
 
 template <int MB, int EPI>
 static void launch_stream_mb(const GemmArgs& a, int nx, hipStream_t s) {
-  constexpr bool cond = EPI == EPI_SILU || EPI == EPI_MOD;
   const dim3 grid(nx, (a.M + 16 * MB - 1) / (16 * MB) * a.splits, a.batch);
-  if constexpr (MB > 4)
-    launch_stream_ring<MB, EPI, false>(a, grid, s);
-  else if (cond || (int64_t)grid.x * grid.y * grid.z > 256)
-    launch_stream_ring<MB, EPI, true>(a, grid, s);
+  if (MB != 4 || EPI == EPI_SILU || EPI == EPI_MOD || (int64_t)grid.x * grid.y * grid.z > 256)
+    launch_stream_ring<MB, EPI>(a, grid, s);
   else
-    launch_stream_ring<MB, EPI, cond>(a, grid, s);
+    launch_stream_ring<MB, EPI, MB == 4 && EPI != EPI_SILU && EPI != EPI_MOD>(a, grid, s);
 }
 
 template <int EPI>
