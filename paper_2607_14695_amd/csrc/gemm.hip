@@ -1913,10 +1913,18 @@ static void launch_skinny_lds_pick(const GemmArgs& a, hipStream_t s) {
   launch_skinny_lds_cfg<MB, EPI>(a, s, nw);
 }
 
+// Both operands can be copied to LDS in 16-byte chunks: a caller's weights or
+// frames may start anywhere (a view into a larger buffer), and only the fragment
+// loads take every address.
+static bool stream_aligned(const GemmArgs& a) {
+  const uint64_t at = (uint64_t)(uintptr_t)a.A | (uint64_t)(uintptr_t)a.B;
+  return at % 16 == 0 && (a.lda | a.ldb | a.a_bstride | a.b_bstride) % 8 == 0;
+}
+
 template <typename T, int EPI>
 static void launch_skinny(const GemmArgs& a, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
-    if (a.M > 16 && a.k_per_split % 32 == 0 && a.K % 32 == 0) {
+    if (a.M > 16 && a.k_per_split % 32 == 0 && a.K % 32 == 0 && stream_aligned(a)) {
       launch_stream<EPI>(a, s);
       return;
     }
@@ -2039,7 +2047,7 @@ static void launch_pick(const GemmArgs& a, hipStream_t s) {
     // (and always where the K split was planned for them)
     constexpr int PAIR = EpiPair<EPI>::value;
     const int nx = PAIR == PAIR_HEAD ? a.N / 32 : (PAIR == PAIR_N ? a.N / 16 : (a.N + 31) / 32);
-    if (a.M > 64 && a.M <= gemm_skinny_rows(2) && a.K % 32 == 0 && a.k_per_split % 32 == 0 &&
+    if (a.M > 64 && a.M <= gemm_skinny_rows(2) && a.K % 32 == 0 && a.k_per_split % 32 == 0 && stream_aligned(a) &&
         nx * stream_chunks(a.M) * a.splits * a.batch <= 256 &&
         (a.M <= 128 || EPI != EPI_F32 || a.k_per_split <= kStreamK))
       skinny = true;

@@ -97,3 +97,40 @@ def test_streamed_frame_projection_beyond_one_wave(batch, tokens):
             for got, ref in ((K[env, l, rows], kf[:, 0]), (Vt[env, l, :, rows], vf[:, 0].T)):
                 assert np.linalg.norm(got - ref) <= 4e-3 * np.linalg.norm(ref), (env, l)
     eng.close()
+
+
+@pytest.mark.parametrize("rows", [17, 33, 64])
+@pytest.mark.parametrize("offset", [1, 2, 4])
+def test_operands_at_any_address(rows, offset):
+    """Weights and frames that start 2, 4 and 8 bytes past a 16-byte boundary (views into a larger buffer): the
+    copies into LDS do not take them, the fragment loads do.  Equal to the oracle as aligned ones are."""
+    import torch
+
+    cfg = BASE.replace(action_horizon=rows - 1, width=192, mlp_dim=320, n_q_heads=3, head_dim=64, frame_dim=96)
+
+    def shifted(a):
+        flat = torch.from_numpy(np.ascontiguousarray(a)).to(torch.bfloat16).cuda().flatten()
+        buf = torch.empty(flat.numel() + 16, dtype=torch.bfloat16, device="cuda")
+        view = buf[offset:offset + flat.numel()].view(a.shape)
+        view.copy_(flat.view(a.shape))
+        assert view.data_ptr() % 16 == 2 * offset and view.is_contiguous()
+        return view
+
+    w = WL.make_weights(cfg)
+    for name in ("w_o", "w_down", "w_aout"):
+        w[name] *= np.float32(4)
+    sk, sv = WL.make_static_kv(cfg)
+    frames = {t: WL.make_frame(cfg, t) for t in range(2)}
+    eng = R.ReflexEngine(cfg, {n: shifted(a) for n, a in w.items()}, sk, sv)
+    for n, a in eng.w.items():
+        assert a.data_ptr() % 16 == 2 * offset, n  # the engine takes them as they are
+    for t in range(2):
+        eng.write_frame(shifted(frames[t]))
+    state, noise = WL.make_state(cfg, 1), WL.make_noise(cfg, 1)
+    got = eng.denoise(state, noise).cpu().numpy()
+    ref = O.denoise_chunk(cfg, w, sk, sv, frames, 2, state, noise, cfg.taus())
+    rel = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    mx = float(np.max(np.abs(got - ref)))
+    print(f"{rows} rows, operands {2 * offset} bytes off: rel-L2 {rel:.2e} max-abs {mx:.2e}", flush=True)
+    assert np.isfinite(got).all() and rel <= BF16_REL and mx <= BF16_ABS, (rel, mx)
+    eng.close()
