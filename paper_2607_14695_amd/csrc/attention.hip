@@ -1959,14 +1959,17 @@ static void launch_attn_dh(const AttnArgs& a, hipStream_t s) {
 
 template <typename T, int DH, int VEC>
 static void launch_merge_vec(const AttnArgs& a, dim3 grid, hipStream_t s) {
-  if (a.nsplit <= 2)
+  if (a.nsplit <= 2) {
     RFX_LAUNCH((attn_merge_kernel<T, DH, VEC, 2>), grid, dim3(256), 0, s, a);
-  else if (a.nsplit <= 4)
+  } else if (a.nsplit <= 4) {
     RFX_LAUNCH((attn_merge_kernel<T, DH, VEC, 4>), grid, dim3(256), 0, s, a);
-  else if (a.nsplit <= 8)
+  } else if (a.nsplit <= 8) {
     RFX_LAUNCH((attn_merge_kernel<T, DH, VEC, 8>), grid, dim3(256), 0, s, a);
-  else
-    RFX_LAUNCH((attn_merge_kernel<T, DH, VEC, kMaxSplits>), grid, dim3(256), 0, s, a);
+  } else {
+    // (the other bf16 forms end at eight splits: launch_merge_dh)
+    if constexpr (sizeof(T) == 4 || (DH == 256 && VEC == 8))
+      RFX_LAUNCH((attn_merge_kernel<T, DH, VEC, kMaxSplits>), grid, dim3(256), 0, s, a);
+  }
 }
 
 template <typename T, int DH>
@@ -1974,15 +1977,20 @@ static void launch_merge_dh(const AttnArgs& a, hipStream_t s) {
   constexpr int V16 = 16 / (int)sizeof(T);
   constexpr int RPB16 = 256 / (DH / V16);
   const int rows = a.T * a.Hq;
+  const int blocks16 = (rows + RPB16 - 1) / RPB16 * a.B;
   if constexpr (sizeof(T) == 2) {
-    // (from nine splits on: one env, 14 splits 3.4 -> 2.9 us, 26 splits 7.7 -> 3.8)
-    if (a.nsplit > 8) {
+    // from nine splits on (one env, 14 splits 3.4 -> 2.9 us, 26 splits 7.7 ->
+    // 3.8), except nine and ten splits that fill the chip with 16-byte threads,
+    // where most groups would hold one split (256-wide heads, 24, 27 and 28
+    // envs of 128 rows: 5.7, 4.9 and 5.8 us, wide 6.0, 5.4 and 6.5; 18 envs, 14
+    // splits 5.8 and 5.1)
+    const bool full = DH == 256 && blocks16 >= 256 && a.nsplit <= 10;
+    if (a.nsplit > 8 && !full) {
       constexpr int RPB = 256 / DH;
       RFX_LAUNCH((attn_merge_wide_kernel<DH>), dim3((rows + RPB - 1) / RPB, a.B), dim3(256), 0, s, a);
       return;
     }
   }
-  const int blocks16 = (rows + RPB16 - 1) / RPB16 * a.B;
   if (sizeof(T) == 4 || blocks16 >= 256) {
     launch_merge_vec<T, DH, V16>(a, dim3((rows + RPB16 - 1) / RPB16, a.B), s);
   } else {

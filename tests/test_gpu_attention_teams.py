@@ -77,3 +77,53 @@ def test_team_attention(case):
             e.write_frame(frames[t])
     for e in engines:
         e.close()
+
+
+# name -> (changes, key splits)
+MERGES = {
+    # 64-wide heads, wide merge: wave pairs with 11 splits of one tile; 16-row waves with 10 splits
+    "wide_64_pairs": (dict(batch=1, n_q_heads=3, head_dim=64, action_horizon=37, static_len=32, frame_tokens=200,
+                           window_frames=3), 11),
+    "wide_64_rows16": (dict(batch=25, n_q_heads=5, head_dim=64, action_horizon=24, static_len=0, frame_tokens=520,
+                            window_frames=2), 10),
+    # 256-wide heads, nine and ten splits in at least 256 16-byte blocks, and eleven (wide)
+    "full_256_9": (dict(batch=28, n_q_heads=4, head_dim=256, action_horizon=31, static_len=0, frame_tokens=264,
+                        window_frames=3), 9),
+    "full_256_10": (dict(batch=25, n_q_heads=3, head_dim=256, action_horizon=27, static_len=0, frame_tokens=648,
+                         window_frames=1), 10),
+    "wide_256_11": (dict(batch=23, n_q_heads=4, head_dim=256, action_horizon=31, static_len=0, frame_tokens=328,
+                         window_frames=2), 11),
+}
+
+
+@pytest.mark.parametrize("case", sorted(MERGES))
+def test_merge_forms(case):
+    """Split merges of nine and more splits on either side of the rule that picks their form, from a partly filled
+    ring (splits without keys) and from a full one, against the oracle."""
+    changes, splits = MERGES[case]
+    cfg = BASE.replace(**changes)
+    rows = cfg.dyn_tokens * cfg.n_q_heads
+    tiles = -(-cfg.cache_rows // 64) + 1
+    base = cfg.batch * -(-rows // 128)
+    groups = cfg.batch * -(-rows // 32) if 256 // base >= tiles else base
+    assert min(256 // groups, tiles, 16) == splits, "not a launch of that many splits"
+    w = WL.make_weights(cfg)
+    for name in ("w_o", "w_aout"):
+        w[name] *= np.float32(8)
+    sk, sv = WL.make_static_kv(cfg)
+    frames = {}
+    eng = R.ReflexEngine(cfg, w, sk, sv)
+    envs = sorted({0, cfg.batch // 2, cfg.batch - 1})
+    for t in range(cfg.window_frames):
+        frames[t] = WL.make_frame(cfg, t)
+        eng.write_frame(frames[t])
+        if t not in (0, cfg.window_frames - 1):
+            continue
+        state, noise = WL.make_state(cfg, t), WL.make_noise(cfg, t)
+        got = eng.denoise(state, noise).cpu().numpy()
+        ref = O.denoise_chunk(cfg, w, sk, sv, frames, t + 1, state, noise, cfg.taus(), envs=envs)
+        rel = float(np.linalg.norm(got[envs] - ref) / np.linalg.norm(ref))
+        mx = float(np.max(np.abs(got[envs] - ref)))
+        print(f"{case} after {t + 1} frames: rel-L2 {rel:.2e} max-abs {mx:.2e}", flush=True)
+        assert np.isfinite(got).all() and rel <= BF16_REL and mx <= BF16_ABS, (t, rel, mx)
+    eng.close()
