@@ -1886,8 +1886,8 @@ __global__ __launch_bounds__(256) void attn_merge_wide_kernel(AttnArgs p) {
 // Query rows per attention workgroup: 128 on the bf16 path, 64 on fp32.
 int attention_rows_per_block(int elem_bytes) { return elem_bytes == 2 ? 128 : 64; }
 
-// Kernel and key-split count for (B envs, rows query rows, up to max_keys
-// cached keys).  One workgroup per CU is resident (LDS bound), so all aim for
+// Kernel and key-split count for (B envs, T dynamic tokens of Hq heads, up to
+// max_keys cached keys).  One workgroup per CU is resident (LDS bound), so all aim for
 // about one wave of workgroups over the 256 CUs.  `base` is the count of
 // 128-row workgroups without a key split.
 //  * one tile per workgroup within one wave as wave pairs (32 rows each): the
@@ -1900,13 +1900,14 @@ int attention_rows_per_block(int elem_bytes) { return elem_bytes == 2 ? 128 : 64
 //    two envs 24.6 -> 14.8 us.  At base 16 (four envs) both take 17.7 us;
 //  * else the 16-row waves, software-pipelined (32 envs 44.7 us against 46.3).
 // `force` (ATTN_ROWS16, ATTN_PAIR or ATTN_ROWS16_PIPE) overrides the choice.
-AttnPlan attention_plan(int B, int rows, int head_dim, int max_keys, int elem_bytes, int force) {
+AttnPlan attention_plan(int B, int T, int Hq, int head_dim, int max_keys, int elem_bytes, int force) {
+  const int rows = T * Hq;
   const int tiles = (max_keys + AKT - 1) / AKT + 1;
   AttnPlan pl;
   pl.kernel = ATTN_ROWS16;
   const int rpb = attention_rows_per_block(elem_bytes);
   int base = B * ((rows + rpb - 1) / rpb);
-  auto fill = [&](int groups, int most) {
+  auto fill = [](int groups, int tiles, int most) {
     int s = 256 / groups;
     if (s > tiles) s = tiles;
     if (s > most) s = most;
@@ -1925,10 +1926,14 @@ AttnPlan attention_plan(int B, int rows, int head_dim, int max_keys, int elem_by
       pl.kernel = ATTN_ROWS16_PIPE;
     }
   }
-  pl.few_splits = pl.splits = fill(groups, kMaxSplits);
+  pl.few_splits = pl.splits = fill(groups, tiles, kMaxSplits);
   if (teams) {
+    // one split per tile counts every dynamic tile: with one split fewer than
+    // tiles, every split that has any takes two (with the merge, four envs of
+    // 126 tokens, two heads of 128, 608 cached keys: 12.4 -> 10.9 us; two envs
+    // of 103 tokens, six heads, 720 keys 12.4 -> 11.1)
     pl.kernel = ATTN_TEAM;
-    pl.splits = fill(base, kMaxTeamSplits);
+    pl.splits = fill(base, tiles + (T - 1) / AKT, kMaxTeamSplits);
   }
   return pl;
 }

@@ -113,7 +113,7 @@ struct AttnPlan {
   int splits;
   int few_splits;  // the count without the team kernel (at most 16)
 };
-AttnPlan attention_plan(int B, int rows, int head_dim, int max_keys, int elem_bytes, int force);
+AttnPlan attention_plan(int B, int T, int Hq, int head_dim, int max_keys, int elem_bytes, int force);
 
 // Precision of the residual stream and of the RMS statistics.  NORM_FP32 is
 // the method (fp32 statistics, Section 3.2); the other two reproduce the

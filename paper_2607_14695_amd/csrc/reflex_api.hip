@@ -159,7 +159,7 @@ Plan make_plan(const reflex_config* c) {
   const int Ko = c->n_q_heads * c->head_dim;
   p.o = make_split(p.M, Ko, gemm_pick_splits(p.M, c->width, Ko, eb), eb);
   p.down = make_split(p.M, c->mlp_dim, gemm_pick_splits(p.M, c->width, c->mlp_dim, eb), eb);
-  const AttnPlan ap = attention_plan(c->batch, rows, c->head_dim, p.R, eb, c->attn_kernel);
+  const AttnPlan ap = attention_plan(c->batch, p.T, c->n_q_heads, c->head_dim, p.R, eb, c->attn_kernel);
   p.attn_splits = ap.splits;
   p.attn_kernel = ap.kernel;
 
