@@ -1887,12 +1887,17 @@ __global__ __launch_bounds__(256) void attn_merge_wide_kernel(AttnArgs p) {
 int attention_rows_per_block(int elem_bytes) { return elem_bytes == 2 ? 128 : 64; }
 
 // Kernel and key-split count for (B envs, T dynamic tokens of Hq heads, up to
-// max_keys cached keys).  One workgroup per CU is resident (LDS bound), so all aim for
-// about one wave of workgroups over the 256 CUs.  `base` is the count of
-// 128-row workgroups without a key split.
+// max_keys cached keys).  One workgroup per CU is resident (LDS bound), so all
+// aim for about one wave of workgroups over the 256 CUs.  `base` is the count
+// of 128-row workgroups without a key split.
 //  * one tile per workgroup within one wave as wave pairs (32 rows each): the
 //    launch is latency-bound and the pair kernel's (one env, 816 cached keys:
-//    10.4 us with the merge against 11.2 us with teams);
+//    10.4 us with the merge against 11.2 us with teams).  With heads of 128
+//    also two tiles, in up to eight splits: the tiles are half as long, and
+//    teams would leave the merge more partials (11 envs of 15 tokens, 8 heads,
+//    432 keys 9.1 us, teams 10.1; 5 envs of 36 tokens, 7 heads, 696 keys 10.3
+//    and 11.4; from nine splits on both take the wide merge and teams are as
+//    fast or faster: one env of 55 tokens, 10 heads, 928 keys 10.0 and 9.4);
 //  * else base < 16 (more than 16 key splits fill the chip), heads of 128 or
 //    256: the team kernel, up to 64 splits.  With the merge, against the
 //    former limit of 16 splits: one env with 3,888 / 15,408 / 38,448 cached
@@ -1918,7 +1923,9 @@ AttnPlan attention_plan(int B, int T, int Hq, int head_dim, int max_keys, int el
   if (elem_bytes == 2) {
     const int pairs = B * ((rows + 31) / 32);
     const bool latency = 256 / base >= tiles;
-    teams = force == ATTN_AUTO && head_dim >= 128 && base < 16 && pairs * tiles > 256;
+    const int pair_splits = fill(pairs, tiles, kMaxSplits);
+    const bool two_tiles = head_dim == 128 && latency && pair_splits <= 8 && tiles <= 2 * pair_splits;
+    teams = force == ATTN_AUTO && head_dim >= 128 && base < 16 && pairs * tiles > 256 && !two_tiles;
     if (force == ATTN_PAIR || (force == ATTN_AUTO && latency)) {
       pl.kernel = ATTN_PAIR;
       groups = pairs;

@@ -57,3 +57,20 @@ def test_one_split_per_tile_counts_every_dynamic_tile(heads, tokens):
             room = min(256 // (batch * P.ceil(tokens * heads, 128)), 64)
             assert P.ceil(tiles, ap.splits) == P.ceil(tiles, min(room, tiles)), (batch, keys, ap.splits)
     assert teams >= 20
+
+
+@pytest.mark.parametrize("batch,tokens,heads,head_dim,keys,kernel,splits", [
+    (11, 15, 8, 128, 432, 2, 5),   # two tiles per split in five splits: wave pairs
+    (5, 36, 7, 128, 696, 2, 6),
+    (2, 87, 9, 128, 296, 2, 5),
+    (11, 15, 8, 128, 960, 4, 16),  # more than two tiles per split: teams
+    (1, 55, 10, 128, 928, 4, 16),  # nine and more splits as pairs
+    (11, 15, 8, 256, 432, 4, 8),   # wider heads
+    (1, 51, 8, 256, 816, 2, 14),   # one tile per pair
+    (4, 51, 8, 256, 1584, 3, 16),  # 16 workgroups of 128 rows
+])
+def test_attention_kernel_of_a_few_envs(batch, tokens, heads, head_dim, keys, kernel, splits):
+    cfg = WL.CONFIGS["tiny_fp32"].replace(name="few", dtype="bf16", batch=batch, head_dim=head_dim, n_q_heads=heads,
+                                          action_horizon=tokens - 1, static_len=0, frame_tokens=keys, window_frames=1)
+    ap = P.attention_plan(cfg)
+    assert (ap.kernel, ap.splits) == (kernel, splits)
