@@ -6,6 +6,7 @@ import pytest
 from oracle import reflex_oracle as O
 from paper_2607_14695_amd import reflex as R
 from paper_2607_14695_amd import workloads as WL
+from tests import plan_model as P
 
 pytestmark = pytest.mark.gpu
 
@@ -17,9 +18,9 @@ BASE = WL.CONFIGS["tiny_fp32"].replace(
     frame_tokens=24, window_frames=2, frame_dim=0, mod_mode="scale_only", batch=1)
 
 
-def _check(cfg, head=4):
+def _check(cfg, head=4, branch=4, mod=1):
     w = WL.make_weights(cfg)
-    for name, scale in (("w_o", 4), ("w_down", 4), ("w_aout", head)):
+    for name, scale in (("w_o", branch), ("w_down", branch), ("w_aout", head), ("w_mod2", mod)):
         w[name] *= np.float32(scale)  # exact in bf16; the actions depend on every projection
     sk, sv = WL.make_static_kv(cfg)
     frames = {t: WL.make_frame(cfg, t) for t in range(2)}
@@ -58,13 +59,43 @@ def test_streamed_row_chunks(batch, tokens):
 @pytest.mark.parametrize("changes", [
     # 300 rows, 64-row tiles: 5, 6 and 27 stages of 64, a last row tile of 44 rows, 320 columns
     dict(batch=5, action_horizon=59, width=320, mlp_dim=1728, n_q_heads=3, head_dim=128, frame_dim=320),
-    # 2,100 rows, 128-row tiles for the gate|up projection: 15 stages; 64-row ones for the others
+    # 2,100 rows: 15 stages, 128-row tiles for gate|up (17 x 14), output and down (17 x 8) projections; QKV
+    # (4 x 33) on 64-row ones
     dict(batch=25, action_horizon=83, width=960, mlp_dim=896, n_q_heads=2, head_dim=128, n_layers=1, num_steps=1),
 ])
 def test_odd_stage_counts(changes):
-    """More than 256 rows with K ranges of no power-of-two stage count: every epilogue of the two-group tiles
-    (fp32, RoPE, gated GELU, and the frame K/V projection of 320 rows with 5 stages)."""
+    """More than 256 rows with K ranges of no power-of-two stage count, on the two-group tiles: the fp32, RoPE and
+    gated-GELU epilogues, and the frame K/V projection of 320 rows with 5 stages."""
     _check(BASE.replace(frame_tokens=64, **changes))
+
+
+def test_two_group_tiles_split_k():
+    """300 rows on the two-group tiles with two K splits of 9 stages (down projection of 1,152 columns)."""
+    cfg = BASE.replace(batch=5, action_horizon=59, width=320, mlp_dim=1152, n_q_heads=3, head_dim=128)
+    assert P.pick_splits(cfg, cfg.width, cfg.mlp_dim) == 2
+    _check(cfg)
+
+
+@pytest.mark.parametrize("mod_mode", ["scale_only", "full"])
+@pytest.mark.parametrize("n_layers", [1, 3, 10])
+def test_two_group_tiles_conditioning(n_layers, mod_mode):
+    """288 conditioning rows (nine steps of 32 envs): the first MLP has 6 stages of K, the second 5 and one slice
+    per site (3, 7 and 21 of them).  Modulations on 64-row tiles with 3 sites (120 tiles), on 128-row ones with 7
+    (168), on the two-stage kernel with 21; the first MLP on 64-row tiles up to 7 sites, on 128-row ones with 21
+    (53 x 5 64-row tiles)."""
+    _check(BASE.replace(batch=32, num_steps=9, n_layers=n_layers, width=320, state_dim=64, cond_hidden=320,
+                        mlp_dim=64, n_q_heads=1, head_dim=64, action_horizon=3, static_len=0, frame_tokens=16,
+                        mod_mode=mod_mode), branch=4 if n_layers < 10 else 1, mod=4)
+
+
+@pytest.mark.parametrize("changes", [
+    dict(batch=6, action_horizon=49, width=320, n_q_heads=3, frame_tokens=104, frame_dim=96),   # 300 and 624 rows
+    dict(batch=2, action_horizon=127, width=192, n_q_heads=5, frame_tokens=136, frame_dim=160),  # 256 and 272
+    dict(batch=13, action_horizon=100, width=576, n_q_heads=2, frame_tokens=24, frame_dim=320),  # 1,313 and 312
+])
+def test_streamed_64_wide_heads(changes):
+    """64-wide heads: QKV and the frame K/V projection are streamed at every row count, in row ranges of 128."""
+    _check(BASE.replace(mlp_dim=320, head_dim=64, **changes))
 
 
 @pytest.mark.parametrize("rows", [17, 32, 33, 64])

@@ -18,6 +18,7 @@ import torch
 from oracle import reflex_oracle as O
 from paper_2607_14695_amd import reflex as R
 from paper_2607_14695_amd import workloads as WL
+from tests import plan_model as P
 
 pytestmark = pytest.mark.gpu
 
@@ -79,6 +80,17 @@ def test_static_entry_equals_graph_entry_two_calls(dtype):
     small = BASE.replace(name=f"noalloc_small_{dtype}", dtype=dtype, batch=1, action_horizon=5)
     _run(big, 5)
     _run(small, 2)
+
+
+def test_static_entry_with_plain_split_counts():
+    """A chunk that fits the static array only with the plain split counts (4 key splits instead of 10 for the team
+    kernel, 66.5 of 67.1 MB): accepted, equal to the graph entry, both against the oracle."""
+    cfg = BASE.replace(name="noalloc_plain_splits", dtype="bf16", batch=14, width=3328, mlp_dim=128, n_q_heads=1,
+                       head_dim=128, action_horizon=121, static_len=32, frame_tokens=112, window_frames=4, frame_dim=0,
+                       n_layers=1, num_steps=2, mod_mode="scale_only")
+    ap = P.attention_plan(cfg)
+    assert P.plans(cfg)[3] and ap.kernel == 4 and ap.splits > ap.few_splits > 1
+    _run(cfg, 5)
 
 
 def test_static_entry_rejects_oversized_chunks():
