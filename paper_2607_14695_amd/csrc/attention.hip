@@ -1695,6 +1695,8 @@ __global__ __launch_bounds__(512) void attn_team_kernel(AttnArgs p) {
   }
 
   // ---- results through LDS -------------------------------------------------
+  // always as partials: fewer than 16 workgroups without a key split and more
+  // keys than wave pairs of one tile cover give at least four splits
   // (the barrier below also ends every read of the K buffers, which the output
   // rows reuse: 128 rows of KRB bytes)
   if (s_on) {
@@ -1707,24 +1709,22 @@ __global__ __launch_bounds__(512) void attn_team_kernel(AttnArgs p) {
     if (c < nbt) {
       const int row = trow + c * 32 + r32;  // within the workgroup
       const float l = xm[team][0][c * 32 + r32] + xm[team][1][c * 32 + r32];
-      const float f = p.nsplit == 1 ? (l > 0.f ? 1.f / l : 0.f) : 1.f;
 #pragma unroll
       for (int a = 0; a < NDW; ++a)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
           *reinterpret_cast<uint2*>(kb + row * KRB + (((db0 + a) * 4 + q4) ^ (row & 15)) * 16 + h * 8) =
-              make_uint2(pack_bf16x2(o[a][c][4 * q4] * f, o[a][c][4 * q4 + 1] * f),
-                         pack_bf16x2(o[a][c][4 * q4 + 2] * f, o[a][c][4 * q4 + 3] * f));
-      if (p.nsplit > 1 && tw == 0 && h == 0 && wrow0 + row < nrows) {
+              make_uint2(pack_bf16x2(o[a][c][4 * q4], o[a][c][4 * q4 + 1]),
+                         pack_bf16x2(o[a][c][4 * q4 + 2], o[a][c][4 * q4 + 3]));
+      if (tw == 0 && h == 0 && wrow0 + row < nrows) {
         const int64_t prow = ((int64_t)b * p.nsplit + split) * p.rows_pad + wrow0 + row;
         *reinterpret_cast<float2*>(p.part_ml + prow * 2) = make_float2(m_run[c], l);
       }
     }
   }
   bar();
-  T* const dst = p.nsplit == 1 ? reinterpret_cast<T*>(p.out) + ((int64_t)b * nrows + wrow0) * DH
-                               : reinterpret_cast<T*>(p.part_o) +
-                                     (((int64_t)b * p.nsplit + split) * p.rows_pad + wrow0) * DH;
+  T* const dst =
+      reinterpret_cast<T*>(p.part_o) + (((int64_t)b * p.nsplit + split) * p.rows_pad + wrow0) * DH;
   for (int e = threadIdx.x; e < wrows * KCH; e += 512) {
     const int row = e / KCH, c = e % KCH;
     st16(dst + (int64_t)row * DH + c * 8,
@@ -2015,8 +2015,8 @@ template <typename T>
 hipError_t launch_attention(const AttnArgs& a, int head_dim, hipStream_t s) {
   if (a.nsplit < 1 || a.nsplit > (a.kernel == ATTN_TEAM ? kMaxTeamSplits : kMaxSplits) || a.rows_pad % 128)
     return hipErrorInvalidValue;
-  if (a.kernel < ATTN_ROWS16 || a.kernel > ATTN_TEAM || (a.kernel == ATTN_TEAM && (head_dim < 128 || sizeof(T) != 2)))
-    return hipErrorInvalidValue;
+  if (a.kernel < ATTN_ROWS16 || a.kernel > ATTN_TEAM) return hipErrorInvalidValue;
+  if (a.kernel == ATTN_TEAM && (head_dim < 128 || sizeof(T) != 2 || a.nsplit < 2)) return hipErrorInvalidValue;
   switch (head_dim) {
     case 64: launch_attn_dh<T, 64>(a, s); break;
     case 128: launch_attn_dh<T, 128>(a, s); break;

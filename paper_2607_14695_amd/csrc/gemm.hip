@@ -1240,8 +1240,8 @@ __global__ __launch_bounds__(512) void gemm_pp(GemmArgs p) {
   constexpr int MB = BM / 32;           // A copies per output block and stage
   constexpr int MB2 = BM / 64;          // 32-row blocks of a wave
   constexpr int CPS = MB + 4;           // copies per output block and stage
-  constexpr int CPW = (CPS + 1) / 2;    // copies per wave and stage (an odd count repeats the last)
-  static_assert(BM == 128 || BM == 64, "128- or 64-row tiles");
+  constexpr int CPW = CPS / 2;          // copies per wave and stage
+  static_assert((BM == 128 || BM == 64) && CPS % 2 == 0, "128- or 64-row tiles, copies in two equal shares");
   __shared__ __attribute__((aligned(16))) unsigned char smem[NS * STB];
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1278,7 +1278,7 @@ __global__ __launch_bounds__(512) void gemm_pp(GemmArgs p) {
     const int rr = lane >> 3, pc = lane & 7;
 #pragma unroll
     for (int i = 0; i < CPW; ++i) {
-      const int j = min(wk * CPW + i, CPS - 1);
+      const int j = wk * CPW + i;
       const bool isa = j < MB;
       const int row0 = isa ? 8 * (MB * wq + j) : 8 * (4 * wq + j - MB);
       const int row = row0 + rr;
