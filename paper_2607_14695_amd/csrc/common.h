@@ -98,17 +98,20 @@ RFX_DEV uint4 f_to_frag(const float* in, bf16_t) {
 }
 
 // Copy of 16 bytes per lane from global memory into LDS (global_load_lds,
-// LDS destination from M0), issued through inline assembly: the compiler
-// then does not track these LDS writes and waits for its own LDS reads with
-// partial counts instead of draining every outstanding read first.  Every
-// kernel that uses it orders the copies itself: a vmcnt(0) wait and a
-// barrier come before any read of a stage, and no stage is overwritten
-// before a barrier that follows its last read.  Outstanding copies it does
-// not know of only make the compiler's own vmcnt waits stricter (loads
-// complete in order).  M0 is a reserved register the compiler sets right
-// before each instruction of its own that reads it, so it is not declared
-// clobbered (it cannot be); the kernels using this helper contain no other
-// M0 reader.
+// LDS destination from M0; the source 16-byte aligned), issued through inline
+// assembly: the compiler then does not track these LDS writes and waits for
+// its own LDS reads with partial counts instead of draining every outstanding
+// read first.  Every kernel that uses it orders the copies itself: before a
+// stage is read, each wave waits for its own share of it and a barrier
+// follows, and no stage is overwritten before a barrier that follows its last
+// read.  The wait is vmcnt(0), or, with several stages in flight, the count of
+// the copies issued after that stage: then every wave issues the same number
+// of copies per stage, stage after stage.  Outstanding copies the compiler
+// does not know of only make its own vmcnt waits stricter, and loads of its
+// own only these (loads complete in order).  M0 is a reserved register the
+// compiler sets right before each instruction of its own that reads it, so it
+// is not declared clobbered (it cannot be); the kernels using this helper
+// contain no other M0 reader.
 RFX_DEV void lds_dma16(const void* g, void* lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                :: "v"(g), "s"((unsigned)(size_t)lds) : "memory");

@@ -15,19 +15,25 @@
 // into the layouts the attention kernel reads.
 //
 // Two regimes:
-//  * weight streaming (M <= 128 on the bf16 path, 64 on the fp32 path).  At one
-//    environment the activations are 51 rows while every weight byte is read
-//    once per Euler step.  A workgroup owns a 32-column strip (or a 16 + 16
-//    paired strip) and a K range and all or some of the rows; the waves'
-//    partial tiles are summed through LDS.  K may be split across workgroups
-//    for the plain fp32 epilogue; the consumer (the residual/norm kernel) sums
-//    the split partials, so no atomics and no extra launch.  gemm_stream copies
-//    both operands into LDS (bf16, more than 16 rows), gemm_skinny_lds only the
+//  * weight streaming: few rows, so that the weights are most of what there is
+//    to read (one environment: 51 rows, every weight byte once per Euler step).
+//    fp32 up to 64 rows; bf16 up to 64, up to 256 where the strips fit one wave
+//    of workgroups, and at any row count for QKV and the frame K/V of 64-wide
+//    heads.  A workgroup owns a 32-column strip (or a 16 + 16 paired strip) and
+//    a K range and all or some of the rows; the waves' partial tiles are summed
+//    through LDS.  K may be split across workgroups for the plain fp32
+//    epilogue; the consumer (the residual/norm kernel) sums the split partials,
+//    so no atomics and no extra launch.  gemm_stream copies both operands into
+//    LDS (bf16, more than 16 rows, 16-byte aligned), gemm_skinny_lds only the
 //    activations (bf16, up to 16 rows: the conditioning MLPs), gemm_skinny
-//    fetches both as fragments (fp32, or a K range that is no multiple of 32).
-//  * gemm_tiled (more rows): 128x128 workgroup tiles, 2x2 waves of 64x64, two
-//    k-steps (128 bytes of K per row) per LDS stage, double-buffered LDS with
-//    the next stage's global loads in flight during the MFMAs.
+//    fetches both as fragments (fp32, other alignments, or a K range that is no
+//    multiple of 32).
+//  * tiles (more rows): bf16 through LDS copies, 256x256 (gemm_big, gemm_big5),
+//    64 to 160 x 128 on rings of four stages or two (gemm_dma) or in two wave
+//    groups (gemm_pp); fp32, and bf16 shapes the copies do not take, on
+//    gemm_tiled: 128x128, 2x2 waves of 64x64, two k-steps (128 bytes of K per
+//    row) per LDS stage, double-buffered LDS with the next stage's global loads
+//    in flight during the MFMAs.
 #include "common.h"
 #include "kernels.h"
 
@@ -830,8 +836,8 @@ RFX_DEV bool dma_tile(const GemmArgs& p, int& bx, int& by, int& bz) {
 // within a group, so that the tiles of one XCD form about a square.  The
 // two-group kernel takes it (26 x 8 tiles of the down projection at 32 envs
 // and 101 tokens, K = 4096: an XCD's tiles span 11 MB of A and B instead of
-// 27; 42.4 -> 35.9 us); on the unrolled pipeline it was not faster (long
-// context, chunk 16.80 -> 16.97 ms).
+// 27; in the chunk's graph 38.0 -> 36.0 us); on the unrolled pipeline it was not
+// faster (long context, chunk 16.80 -> 16.97 ms).
 template <int PAIR, int BM>
 RFX_DEV bool group_tile(const GemmArgs& p, int& bx, int& by, int& bz) {
   const int nx = PAIR == PAIR_NONE ? (p.N + TBN - 1) / TBN : p.N / (PAIR == PAIR_N ? 64 : 128);
@@ -1210,8 +1216,8 @@ __global__ __launch_bounds__(256 * KW) void gemm_dma(GemmArgs p) {
 // --------------------------------------------------------------------------
 // tiled, bf16, BM x 128 tiles, any number of stages: the one-wave grids whose K
 // range is none of the unrolled pipeline's (8, 16 or 32 stages), which ran on
-// the two-stage kernel (down projection of 3,232 rows, 64 stages: 71.9 -> 37.2
-// us).  Two wave groups run half a stage apart.  Four output blocks (2 x 2 of
+// the two-stage kernel (down projection of 3,232 rows, 64 stages, in the chunk's
+// graph: 71.5 -> 36.0 to 37.6 us on two cards).  Two wave groups run half a stage apart.  Four output blocks (2 x 2 of
 // BM/2 x 64) have two waves each, one per 32-wide k-step of a 64-element stage;
 // the waves of k-step 0 are group 0, those of k-step 1 group 1, and every SIMD
 // holds one wave of each.  While one group issues the MFMAs of a stage, the
@@ -1980,10 +1986,11 @@ static void launch_tiled(const GemmArgs& a, hipStream_t s) {
       while ((gm + 1) * gm * bm <= (tiles(bm) + 7) / 8 * TBN) ++gm;
       t.tile_group = gm < ny ? gm : ny;
     };
-    // four-stage unrolled pipeline (one workgroup per CU) when one wave of
-    // workgroups covers the grid; else the two-stage one (two per CU).  The
-    // stage count is that of every split's K range (a single split may be
-    // given a range past K: its range is then K).
+    // when one wave of workgroups covers the grid, one workgroup per CU: the
+    // four-stage unrolled pipeline at 8, 16 or 32 stages, gemm_pp at any other
+    // count; else the two-stage one (two per CU).  The stage count is that of
+    // every split's K range (a single split may be given a range past K: its
+    // range is then K).
     const int kr1 = a.splits == 1 ? a.K : (a.K == a.k_per_split * a.splits ? a.k_per_split : 0);
     const int nst = kr1 % DST == 0 ? kr1 / DST : 0;
     // just over one wave of 128-row tiles with a 16-stage K range: 160-row

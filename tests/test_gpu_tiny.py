@@ -278,9 +278,9 @@ def test_gemm_row_tilings_bf16(batch, width):
     output) GEMMs take the tiled path with 64-row tiles on the four-stage
     pipeline, 8 stages of 64 over K = 512 at width 512 and 32 stages at width
     2048 (QKV and gate|up with two waves per output block).  One env (M = 51):
-    the unsplit skinny GEMMs with few column strips (QKV, gate|up) take their
-    rows in two 32-row halves, and the split merge its 4-byte form.  Every env
-    is checked against the oracle within the bf16 tolerance."""
+    the streaming GEMMs take their rows in two ranges of 32 where the strips
+    are few, and the split merge its 4-byte form.  Every env is checked
+    against the oracle within the bf16 tolerance."""
     cfg = RAGGED.replace(name=f"rowtile_bf16_b{batch}_w{width}", dtype="bf16", batch=batch, action_horizon=50, width=width,
                          mlp_dim=512, n_q_heads=2, head_dim=128, frame_dim=0, n_layers=1, num_steps=2,
                          window_frames=2)
