@@ -70,10 +70,11 @@ extern "C" {
  * over [static; ring window; dynamic] (Eq. 1) and agree to rounding.
  * REFLEX_ATTN_AUTO picks by the launch geometry: one wave pair per 32 query
  * rows when the launch would reach one key tile per split (a few envs and a
- * short context), two four-wave teams per 128 query rows with up to 64 key
- * splits (a few envs, more keys, head_dim 128 or 256), otherwise 16-row waves
- * sharing each key tile over 128 query rows, software-pipelined (a tile's
- * scores and softmax run under the previous tile's P.V MFMAs).  REFLEX_ATTN_ROWS16 forces the 16-row kernel
+ * short context; heads of 128 also two), two four-wave teams per 128 query
+ * rows with up to 64 key splits (a few envs, more keys, head_dim 128 or 256),
+ * otherwise 16-row waves sharing each key tile over 128 query rows,
+ * software-pipelined (a tile's scores and softmax run under the previous
+ * tile's P.V MFMAs).  REFLEX_ATTN_ROWS16 forces the 16-row kernel
  * without that pipelining (the same results bit for bit); the other values
  * force one kernel (tests, tuning).  The fp32 path has one kernel and
  * ignores the field. */

@@ -1233,7 +1233,7 @@ __global__ __launch_bounds__(128) void attn_pair_kernel(AttnArgs p) {
 // The probabilities go through LDS between the two (8 KB per team and tile).
 // A K, V^T or P fragment read feeds 32 rows instead of 16: 256 KB of LDS
 // reads per tile and 128 rows, against 512 KB when every wave reads the whole
-// tile for 16 rows of its own, which bounded that kernel.
+// tile for 16 rows of its own, the largest part of that kernel's chain.
 //
 // The teams run half a tile apart (every SIMD holds one wave of each): while
 // one issues its MFMAs (P.V of tile t-1, then the scores of tile t), the
@@ -1901,7 +1901,7 @@ int attention_rows_per_block(int elem_bytes) { return elem_bytes == 2 ? 128 : 64
 //  * else base < 16 (more than 16 key splits fill the chip), heads of 128 or
 //    256: the team kernel, up to 64 splits.  With the merge, against the
 //    former limit of 16 splits: one env with 3,888 / 15,408 / 38,448 cached
-//    keys 19.5 -> 15.5, 41.5 -> 22.5, 88.5 -> 35.4 us; 101 tokens 27.0 -> 15.0;
+//    keys 19.5 -> 15.5, 41.5 -> 22.5, 88.5 -> 35.4 us; 101 tokens 27.5 -> 14.5;
 //    two envs 24.6 -> 14.8 us.  At base 16 (four envs) both take 17.7 us;
 //  * else the 16-row waves, software-pipelined (32 envs 44.7 us against 46.3).
 // `force` (ATTN_ROWS16, ATTN_PAIR or ATTN_ROWS16_PIPE) overrides the choice.

@@ -469,8 +469,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_lds(GemmArgs p) {
 // 16-byte chunks are XOR-swizzled by (row mod 16).  Against the activations
 // in LDS and the weights as fragments, one env (51 rows): output projection
 // 5.7 -> 4.4 us, gate|up 8.3 -> 7.1 (16.8 MB of weights), down 6.6 -> 5.4, QKV
-// 6.4 -> 6.0; against the 128x128 tiles, 101 rows: QKV 11.1 -> 7.0, output
-// projection 7.0 -> 5.3, gate|up 10.1 -> 8.6; a 576-wide expert with 114 rows
+// 6.4 -> 6.0 (5.4 with the ring of four); against the 128x128 tiles, 101 rows:
+// QKV 11.1 -> 7.0, output projection 7.0 -> 5.3, gate|up 10.1 -> 8.6; a
+// 576-wide expert with 114 rows
 // (K of 576, 640 and 1728, few column tiles): 15.3 -> 4.7, 11.9 -> 3.4,
 // 11.5 -> 5.2, down 23.5 -> 4.5 us.
 // --------------------------------------------------------------------------
